@@ -32,7 +32,7 @@ SHAPES = {
                  dtype="f32"),
 }
 # The head of a `layers` case: the call always ends in a head, and a small one
-# keeps the layers the measured part (the full head has cases of its own).
+# over four layers keeps the layers the measured part (the full head has cases of its own).
 LAYERS_VOCAB = 2048
 TOPK, ALPHA = 5, 0.4
 
@@ -50,26 +50,26 @@ def listed():
         dict(name="whole_llada_120", kind="whole", model="llada8b", layers=32, batch=1, prompt=256,
              gen=256, block=32, block_idx=3, cache=True, local=64, middle=16, tail=8),
         # The same cached step in middle layers alone: what 31 of 32 steps of a short generation do.
-        dict(name="layers_decode_120", kind="layers", model="llada8b", layers=2, act="one", batch=1,
+        dict(name="layers_decode_120", kind="layers", model="llada8b", layers=4, act="one", batch=1,
              cached=352, prefix=0, block=32, suffix=88, ragged=False),
         # A cached step of a long generation: 240 rows over 1776 keys.
-        dict(name="layers_decode_240", kind="layers", model="llada8b", layers=2, act="one", batch=1,
+        dict(name="layers_decode_240", kind="layers", model="llada8b", layers=4, act="one", batch=1,
              cached=1536, prefix=0, block=64, suffix=176, ragged=False),
         # A small served batch whose prompts differ in length.
-        dict(name="layers_decode_b4_ragged", kind="layers", model="llada8b", layers=2, act="one",
+        dict(name="layers_decode_b4_ragged", kind="layers", model="llada8b", layers=4, act="one",
              batch=4, cached=320, prefix=0, block=32, suffix=87, ragged=True),
         # A large served batch: 32 sequences, 3840 rows in one cached step.
-        dict(name="layers_decode_b32", kind="layers", model="llada8b", layers=2, act="one",
+        dict(name="layers_decode_b32", kind="layers", model="llada8b", layers=4, act="one",
              batch=32, cached=352, prefix=0, block=32, suffix=88, ragged=False),
         # The first step of a block of a short generation in the leading layers, which keep the
         # projection inputs as a pair.
-        dict(name="layers_start_376_pair", kind="layers", model="llada8b", layers=2, act="pair",
+        dict(name="layers_start_376_pair", kind="layers", model="llada8b", layers=4, act="pair",
              batch=1, cached=0, prefix=256, block=32, suffix=88, ragged=False),
         # The first step of a block in the middle of a long generation.
-        dict(name="layers_start_1776", kind="layers", model="llada8b", layers=2, act="one", batch=1,
+        dict(name="layers_start_1776", kind="layers", model="llada8b", layers=4, act="one", batch=1,
              cached=0, prefix=1536, block=64, suffix=176, ragged=False),
         # A step without the prefix cache on the grouped-query model, at an odd row count.
-        dict(name="layers_dream_1127", kind="layers", model="dream7b", layers=2, act="one", batch=1,
+        dict(name="layers_dream_1127", kind="layers", model="dream7b", layers=4, act="one", batch=1,
              cached=0, prefix=992, block=32, suffix=103, ragged=False),
         # The head of the flagship step.
         dict(name="head_120", kind="head", model="llada8b", rows=120),
@@ -99,12 +99,12 @@ def draw(rng):
         block, suffix = rng.choice([16, 32, 64]), rng.randrange(20, 200)
         act = rng.choice(["one", "one", "pair"])
         if rng.random() < 0.6:      # cached step, one sequence or a batch
-            batch = _log(rng, 1, 16)
-            return dict(kind="layers", model=model, layers=2, act=act, batch=batch,
+            batch = _log(rng, 1, min(16, 3300 // ((block + suffix) * (2 if act == "pair" else 1))))
+            return dict(kind="layers", model=model, layers=4, act=act, batch=batch,
                         cached=_log(rng, 100, 2500 if batch < 5 else 600), prefix=0, block=block,
                         suffix=suffix, ragged=batch > 1 and rng.random() < 0.5)
-        return dict(kind="layers", model=model, layers=2, act=act, batch=1, cached=0,
-                    prefix=_log(rng, 100, 2000), block=block, suffix=suffix, ragged=False)
+        return dict(kind="layers", model=model, layers=4, act=act, batch=1, cached=0,
+                    prefix=_log(rng, 100, 1300 if act == "pair" else 2000), block=block, suffix=suffix, ragged=False)
     if kind == "head":
         return dict(kind="head", model=rng.choice(["llada8b", "dream7b"]), rows=_log(rng, 16, 480))
     if kind == "attn":
@@ -440,7 +440,7 @@ def tolerance(case):
         return {"rel": 8e-3 if case["dtype"] == "bf16" else 2e-3}
     if kind == "head":         # one bf16 rounding of the normalised row; ties of the top k
         return {"rel": 8e-3, "differ": 0.01}
-    if kind == "layers":       # a few roundings to bf16 and f16 in each of two layers
+    if kind == "layers":       # a few roundings to bf16 and f16 in each of four layers
         return {"rel": 1.2e-2}
     return {"rel": 0.03}       # the same in 32 layers: 1e-2 against 64 bits
 
