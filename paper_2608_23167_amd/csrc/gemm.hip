@@ -32,6 +32,9 @@
 //   LM head: per-row softmax statistics of each half tile (merged later).
 // Split-K writes float32 partial tiles that a second kernel sums in a fixed
 // order before applying the same epilogue.
+//
+// gemm_bf16_kernel above serves the row counts that are bound by the weight
+// stream; gemm_pp_kernel, below, the row counts that are bound by the MFMAs.
 #include <stdio.h>
 #include <stdlib.h>
 #include <string.h>
@@ -61,6 +64,11 @@ __device__ __forceinline__ void store_row8(f16_t* p, const float (&v)[8]) {
 #pragma unroll
   for (int e = 0; e < 8; ++e) h[e] = (f16_t)v[e];
   *(f16x8_t*)p = h;
+}
+
+// Four consecutive row-major elements (8 bytes, aligned).
+__device__ __forceinline__ void store_row4(f16_t* p, f32x4_t v) {
+  *(f16x4_t*)p = __builtin_convertvector(v, f16x4_t);
 }
 
 // Column tile t of width BN covers BN / 2 consecutive entries of the
@@ -144,6 +152,25 @@ struct PolQKV {
     store_row8(dst + i0, a);
     store_row8(dst + i0 + half, b);
   }
+  // columns c0 .. c0 + 3 of both halves (c0 a multiple of 4: one head)
+  __device__ __forceinline__ void store4(int m, int t, int c0, int BN, f32x4_t lo, f32x4_t hi) const {
+    const int half = dh / 2, j = t * (BN / 2) + c0, head = j / half, i0 = j - head * half;
+    const int s = m / n_rows, row = m % n_rows;
+    f32x4_t a = lo, b = hi;
+    if (head < H + Hkv) {
+      const float4* cs = (const float4*)(rope + ((size_t)(rope_per_seq ? s : 0) * n_rows + row) * half + i0);
+      const float4 r0 = cs[0], r1 = cs[1];     // two (cos, sin) pairs each
+      const f32x4_t c = {r0.x, r0.z, r1.x, r1.z}, sn = {r0.y, r0.w, r1.y, r1.w};
+      a = lo * c - hi * sn;
+      b = hi * c + lo * sn;
+    }
+    TO* dst;
+    if (head < H) dst = q + (((size_t)s * H + head) * n_rows + row) * dh;
+    else if (head < H + Hkv) dst = kc + (((size_t)s * Hkv + (head - H)) * cap + n_cached + row) * dh;
+    else dst = vc + (((size_t)s * Hkv + (head - H - Hkv)) * cap + n_cached + row) * dh;
+    store_row4(dst + i0, a);
+    store_row4(dst + i0 + half, b);
+  }
 };
 
 template <typename T>
@@ -167,6 +194,12 @@ struct PolSwiGLU {
     for (int e = 0; e < 8; ++e) v[e] = g[e] / (1.0f + expf(-g[e])) * u[e];
     act.store8<T>(m, t * (BN / 2) + c0, v);
   }
+  __device__ __forceinline__ void store4(int m, int t, int c0, int BN, f32x4_t g, f32x4_t u) const {
+    float v[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = g[e] / (1.0f + expf(-g[e])) * u[e];
+    act.store4(m, t * (BN / 2) + c0, v);
+  }
 };
 
 template <typename T>
@@ -189,6 +222,10 @@ struct PolResid {
     b.x += v[4]; b.y += v[5]; b.z += v[6]; b.w += v[7];
     p[0] = a;
     p[1] = b;
+  }
+  __device__ __forceinline__ void store4_1(int m, int n0, f32x4_t v) const {
+    f32x4_t* p = (f32x4_t*)(resid + (size_t)m * N + n0);
+    *p += v;
   }
 };
 
@@ -574,9 +611,6 @@ __global__ void __launch_bounds__(512) gemm_bf16_kernel(Pol pol, const bf16_t* _
   tile_epilogue<BM, BN, CS>(pol, Cs, m0, M, t, part, split, ldp);
 }
 
-// ---------------------------------------------------------------------------
-// bfloat16 MFMA kernel for many rows (block-start steps of long prompts)
-// ---------------------------------------------------------------------------
 // Waits until at most N vector-memory operations of this wave are in flight.
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {
@@ -584,138 +618,203 @@ __device__ __forceinline__ void wait_vmcnt() {
   __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
 }
 
-// A BM x BN output tile per workgroup of 8 waves in a WM x WN grid; wave
-// (wm, wn) owns rows (BM / WM) wm .. and columns (BN / WN) wn .. (FM x FN MFMA
-// blocks).  Shapes: 256 x 128 (4 x 2 waves) and 128 x 256 (2 x 4).
-// Both operands go from global memory straight into LDS (global_load_lds,
-// 1 KB per instruction) in K-steps of 32, through a ring of two stages:
-//  * activations: the fragment-order operand already holds each 16-row x
-//    32-column MFMA operand as 1 KB, so a stage is BM / 16 such blocks per
-//    part (hi, lo), copied as they are;
-//  * weights: BN / 16 blocks of 16 rows x 32 columns, lane l of a block
-//    holding row l % 16, columns 8 (l / 16) .. + 7: the B-operand layout.
-// Every operand read is then one conflict-free 16-byte LDS load per lane.
-// With 64-80 KB of LDS and at most 128 VGPRs, two workgroups share a CU, so
-// one workgroup's barrier wait overlaps the other's MFMAs.  The output tile
-// goes through LDS in chunks of EB rows into the same epilogues as
-// gemm_bf16_kernel.
-template <int BM, int BN, int WM, int WN, int NS, bool SPLIT, class Pol>
-__global__ void __launch_bounds__(WM * WN * 64, (BM / WM) * (BN / WN) > 4096 ? 2 : 4) gemm_big_kernel(Pol pol, const bf16_t* __restrict__ Ahi,
-                                                          const bf16_t* __restrict__ Alo, int G,
-                                                          int M, int k_per_split, int mt,
-                                                          int n_split, float* __restrict__ part,
-                                                          int ldp) {
-  constexpr int NW = WM * WN;
-  static_assert(NW == 8 || NW == 16, "8 or 16 waves");
-  static_assert(NS == 2 || NS == 3, "ring of 2 or 3 stages");
-  constexpr int BK = 32;
-  constexpr int NA = SPLIT ? 2 : 1;
-  constexpr int GB = BM / 16;                                   // row groups per tile
-  constexpr int A_BLOCKS = GB * NA, BLOCKS = A_BLOCKS + BN / 16;
-  static_assert(BLOCKS % NW == 0, "whole blocks per wave");
-  constexpr int CPW = BLOCKS / NW, STAGE = BLOCKS * 1024;
+// ---------------------------------------------------------------------------
+// bfloat16 MFMA kernel, two wave groups in alternation
+// ---------------------------------------------------------------------------
+// A BM x BN output tile per workgroup of 8 waves in a WM x WN grid, K-steps of
+// 64 in two halves of 32.  Waves w and w + 4 share a SIMD; the waves 4-7 run
+// half a phase behind the waves 0-3, so that on every SIMD one wave issues
+// MFMAs while the other reads its next operands from LDS and starts copies.
+// A phase of a wave is
+//   memory part:  LDS reads of one half K-step's fragments, copies of later
+//                 K-steps (global_load_lds), wait for the reads, barrier;
+//   MFMA part:    FM x FN MFMAs on them, barrier.
+// Barriers number the slots: in slot 4t (even) the first group reads half 0
+// of K-step t, in 4t + 1 the second group does while the first multiplies, and
+// so on.  LDS rings: two stages of activations (BM x 64, each half separate),
+// three of weights (BN x 64).  What a copy overwrites and where it is read:
+//   weights t + 2        stage read last in slot 4t - 1, copied in 4t / 4t + 1,
+//                        read from slot 4t + 8 on;
+//   activations t + 1, half 1: read last in slot 4t - 1, copied in 4t / 4t + 1,
+//                        read from slot 4t + 6 on;
+//   activations t + 2, half 0: read last in slot 4t + 1, copied in 4t + 2 /
+//                        4t + 3, read from slot 4t + 8 on.
+// Each wave waits, before the barrier that opens a slot in which the first
+// group reads, until only its copies of the last two phases are in flight.
+// Copies past the last K-step repeat the last one (never read), which keeps
+// the count uniform.  With SPLIT every K-step runs twice, on the hi and the lo
+// part of the activations with the same weights.
+//
+// Activations are in fragment order: a copy of 1 KB is one MFMA operand and is
+// read back at 16 bytes per lane.  A weight copy covers 8 rows of 128 bytes
+// (whole cache lines); the 16-byte chunk c of row r sits at slot
+// c ^ ((r / 2) % 8), so that the 16 rows of a fragment read fall on 16
+// different 16-byte columns of the banks.
+// The MFMA takes the weights as its first operand: a lane then holds 4
+// consecutive columns of one row, and the epilogue runs from registers.
+__device__ __forceinline__ void pp_barrier() {
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("s_barrier" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+template <int BM, int BN, int WM, int WN, bool SPLIT, class Pol>
+__global__ void __launch_bounds__(512, 2) gemm_pp_kernel(Pol pol, const bf16_t* __restrict__ Ahi,
+                                                           const bf16_t* __restrict__ Alo, int G,
+                                                           int M, int k_steps, int mt,
+                                                           int n_split, float* __restrict__ part,
+                                                           int ldp) {
+  static_assert(WM * WN == 8, "8 waves");
   constexpr int RW = BM / WM, CW = BN / WN, FM = RW / 16, FN = CW / 16;
-  constexpr int CS = BN + 4;
-  constexpr int EB = BN > 128 ? BM / 2 : 128;                   // epilogue chunk rows
-  constexpr int SMEM_W = NS * STAGE, SMEM_C = EB * CS * 4;
-  constexpr int SMEM = SMEM_W > SMEM_C ? SMEM_W : SMEM_C;
-  static_assert(EB % RW == 0, "a wave's rows in one epilogue chunk");
-  __shared__ __attribute__((aligned(1024))) char smem[SMEM];
+  constexpr bool PAIRED = Pol::PAIRED;
+  static_assert(CW % (PAIRED ? 32 : 16) == 0 && RW % 16 == 0, "whole fragments per wave");
+  constexpr int LA = BM / 128, LW = BN / 64;       // copies per wave: half K-step of A, K-step of W
+  static_assert(BM % 128 == 0 && BN % 64 == 0, "whole copies per wave");
+  constexpr int A_HALF = BM * 64, A_STAGE = 2 * A_HALF, W_STAGE = BN * 128;   // bytes
+  constexpr int INFLIGHT = LW + 2 * LA;
+  __shared__ __attribute__((aligned(1024))) char smem[2 * A_STAGE + 3 * W_STAGE];
+  char* const Ws = smem + 2 * A_STAGE;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave % WM, wn = wave / WM;
+  const bool late = wave >= 4;                     // the second group
   int t, mtile, split;
   tile_of(blockIdx.x, gridDim.x, gridDim.x / n_split, mt, split, t, mtile);
   const int m0 = mtile * BM;
-  const int kbeg = split * k_per_split, nk = k_per_split / BK, last = nk - 1;
+  // K-steps of this split: the k_steps of the row dealt out evenly, whole steps
+  const int ks0 = split * k_steps / n_split, kbeg = 64 * ks0;
+  const int nk = ((split + 1) * k_steps / n_split - ks0) * (SPLIT ? 2 : 1), last = nk - 1;
 
-  // this wave's blocks of a stage: block c = wave * CPW + i; c < A_BLOCKS are
-  // activation blocks (part c / GB, row group c % GB), the rest weight blocks
+  // copy sources
   const bf16_t *blo, *bhi;
   pol.b_ptrs(t, BN, blo, bhi);
   const size_t a_kstep = (size_t)G * 1024;
-  const bf16_t* src[CPW];
-  bool is_a[CPW];
+  const bf16_t* w_src[LW];                         // uniform: first row of each 8-row block
 #pragma unroll
-  for (int i = 0; i < CPW; ++i) {
-    const int c = wave * CPW + i;
-    is_a[i] = c < A_BLOCKS;
-    if (c < A_BLOCKS) {
-      const int grp = min((m0 >> 4) + (c % GB), G - 1);   // groups past the allocation: the last
-      src[i] = ((c / GB) ? Alo : Ahi) + (size_t)(kbeg >> 6) * a_kstep + (size_t)grp * 1024 + lane * 8;
-    } else {
-      const int r = 16 * (c - A_BLOCKS) + (lane & 15);
-      src[i] = weight_row(pol, t, BN, r, blo, bhi) + kbeg + 8 * (lane >> 4);
-    }
-  }
-  // K-step ks of the split into the ring slot of K-step kb
-  auto issue = [&](int kb, int ks) {
-    char* dst = smem + (kb % NS) * STAGE + wave * CPW * 1024;
+  for (int i = 0; i < LW; ++i)
+    w_src[i] = weight_row(pol, t, BN, 8 * (wave * LW + i), blo, bhi) + kbeg;
+  // byte offset of this lane's row and chunk in an even / odd block
+  const uint32_t w_off0 = (uint32_t)(lane >> 3) * pol.ldb * 2 + (((lane & 7) ^ (lane >> 4)) << 4);
+  const uint32_t w_off1 = (uint32_t)(lane >> 3) * pol.ldb * 2 + (((lane & 7) ^ (lane >> 4) ^ 4) << 4);
+  int a_grp[LA];
 #pragma unroll
-    for (int i = 0; i < CPW; ++i) {
-      const bf16_t* p = is_a[i] ? src[i] + (size_t)(ks >> 1) * a_kstep + (ks & 1) * 512
-                                : src[i] + (size_t)ks * BK;
-      __builtin_amdgcn_global_load_lds((const void*)p,
-                                       (__attribute__((address_space(3))) void*)(dst + i * 1024),
-                                       16, 0, 0);
-    }
+  for (int i = 0; i < LA; ++i) a_grp[i] = min((m0 >> 4) + wave * LA + i, G - 1);
+
+  // 16 bytes per lane: from a uniform address and a lane's byte offset
+  auto copy = [](const bf16_t* src, uint32_t off, char* dst) {
+    __builtin_amdgcn_global_load_lds((const void*)((const char*)src + off),
+                                     (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
   };
+  // half kk of K-step v (activations), into stage v % 2
+  auto issue_a = [&](int v, int kk) {
+    const int vs = min(v, last), ks = SPLIT ? vs >> 1 : vs;
+    const bf16_t* base = (SPLIT && (vs & 1) ? Alo : Ahi) + (size_t)(ks0 + ks) * a_kstep + kk * 512;
+    char* dst = smem + (v & 1) * A_STAGE + kk * A_HALF + wave * LA * 1024;
+#pragma unroll
+    for (int i = 0; i < LA; ++i) copy(base + (size_t)a_grp[i] * 1024, lane * 16, dst + i * 1024);
+  };
+  // K-step v (weights), into ring slot `slot`
+  auto issue_w = [&](int v, int slot) {
+    const int vs = min(v, last), ks = SPLIT ? vs >> 1 : vs;
+    char* dst = Ws + slot * W_STAGE + wave * LW * 1024;
+#pragma unroll
+    for (int i = 0; i < LW; ++i)
+      copy(w_src[i] + (size_t)ks * 64, ((wave * LW + i) & 1) ? w_off1 : w_off0, dst + i * 1024);
+  };
+
   f32x4_t acc[FM][FN];
 #pragma unroll
   for (int i = 0; i < FM; ++i)
 #pragma unroll
     for (int j = 0; j < FN; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-  // the ring runs NS - 1 K-steps ahead; K-steps past the last one reload the
-  // last (never read), which keeps the count of copies in flight uniform
-#pragma unroll
-  for (int s = 0; s < NS - 1; ++s) issue(s, min(s, last));
-  wait_vmcnt<CPW * (NS - 2)>();
-  __syncthreads();
-  for (int kt = 0; kt < nk; ++kt) {
-    // slot (kt + NS - 1) % NS was last read in step kt - 1, before the last barrier
-    issue(kt + NS - 1, min(kt + NS - 1, last));
-    const char* stg = smem + (kt % NS) * STAGE;
-    bf16x8_t af[NA][FM], wf[FN];
-#pragma unroll
-    for (int p = 0; p < NA; ++p)
-#pragma unroll
-      for (int i = 0; i < FM; ++i)
-        af[p][i] = *(const bf16x8_t*)(stg + (p * GB + FM * wm + i) * 1024 + lane * 16);
-#pragma unroll
-    for (int j = 0; j < FN; ++j)
-      wf[j] = *(const bf16x8_t*)(stg + (A_BLOCKS + FN * wn + j) * 1024 + lane * 16);
-#pragma unroll
-    for (int p = 0; p < NA; ++p)
-#pragma unroll
-      for (int i = 0; i < FM; ++i)
-#pragma unroll
-        for (int j = 0; j < FN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[p][i], wf[j], acc[i][j], 0, 0, 0);
-    // this wave's blocks of step kt + 1 (copies retire in issue order; the
-    // NS - 2 younger stages stay in flight), then all blocks visible and slot
-    // kt free.  A plain barrier: a fenced one would wait for every copy.
-    wait_vmcnt<CPW * (NS - 2)>();
-    asm volatile("s_barrier" ::: "memory");
-  }
-  wait_vmcnt<0>();                                 // the ring is reused by the epilogue
-  __syncthreads();
-  // acc[i][j][r] = C[RW wm + 16 i + 4 (lane / 16) + r][CW wn + 16 j + lane % 16]
-  float* Cs = (float*)smem;
-#pragma unroll
-  for (int h = 0; h < BM / EB; ++h) {
-    if ((RW * wm) / EB == h) {
-#pragma unroll
-      for (int i = 0; i < FM; ++i)
-#pragma unroll
-        for (int j = 0; j < FN; ++j)
-#pragma unroll
-          for (int r = 0; r < 4; ++r)
-            Cs[(RW * wm - h * EB + 16 * i + 4 * (lane >> 4) + r) * CS + CW * wn + 16 * j + (lane & 15)] =
-                acc[i][j][r];
+  bf16x8_t af[FM], wf[FN];
+
+  // LDS offsets of this wave's fragments
+  const int a_frag = wm * FM * 1024 + lane * 16;
+  const int r16 = lane & 15, g4 = lane >> 4;
+  const int w_lane = r16 * 128 + ((g4 ^ (r16 >> 1)) << 4);        // half 0; half 1: chunk ^ 4
+  auto w_rows = [&](int j) {                        // first tile row of weight fragment j
+    if constexpr (PAIRED) {
+      constexpr int HF = FN / 2;
+      return (j < HF ? wn * (CW / 2) + 16 * j : BN / 2 + wn * (CW / 2) + 16 * (j - HF));
+    } else {
+      return wn * CW + 16 * j;
     }
-    __syncthreads();
-    tile_epilogue<EB, BN, CS>(pol, Cs, m0 + h * EB, M, t, part, split, ldp);
-    __syncthreads();
+  };
+  auto read = [&](int v, int slot, int kk) {
+    const char* a = smem + (v & 1) * A_STAGE + kk * A_HALF + a_frag;
+    const char* w = Ws + slot * W_STAGE + (w_lane ^ (kk << 6));
+#pragma unroll
+    for (int j = 0; j < FN; ++j) wf[j] = *(const bf16x8_t*)(w + w_rows(j) * 128);
+#pragma unroll
+    for (int i = 0; i < FM; ++i) af[i] = *(const bf16x8_t*)(a + i * 1024);
+  };
+  auto mma = [&]() {
+    __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int j = 0; j < FN; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[j], af[i], acc[i][j], 0, 0, 0);
+    __builtin_amdgcn_s_setprio(0);
+  };
+  // end of a memory part / of an MFMA part
+  auto end_mem = [&]() {
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14));   // lgkmcnt(0)
+    if (late) wait_vmcnt<INFLIGHT>();
+    pp_barrier();
+  };
+  auto end_mma = [&]() {
+    __builtin_amdgcn_sched_barrier(0);
+    if (!late) wait_vmcnt<INFLIGHT>();
+    pp_barrier();
+  };
+
+  issue_w(0, 0);
+  issue_a(0, 0);
+  issue_a(0, 1);
+  issue_w(1, 1);
+  issue_a(1, 0);
+  wait_vmcnt<LW + LA>();
+  pp_barrier();
+  if (late) pp_barrier();
+  int s0 = 0, s2 = 2;                               // ring slots of K-steps v and v + 2
+  for (int v = 0; v < nk; ++v) {
+    read(v, s0, 0);
+    issue_w(v + 2, s2);
+    issue_a(v + 1, 1);
+    end_mem();
+    mma();
+    end_mma();
+    read(v, s0, 1);
+    issue_a(v + 2, 0);
+    end_mem();
+    mma();
+    end_mma();
+    s2 = s0;
+    s0 = s0 == 2 ? 0 : s0 + 1;
+  }
+  if (!late) pp_barrier();
+  wait_vmcnt<0>();                                  // no copy lands after the workgroup ends
+
+  // acc[i][j][r] = C[RW wm + 16 i + lane % 16][w_rows(j) + 4 (lane / 16) + r]
+#pragma unroll
+  for (int i = 0; i < FM; ++i) {
+    const int m = m0 + wm * RW + 16 * i + r16;
+    if (m >= M) continue;
+    if (part) {
+      float* p = part + ((size_t)split * M + m) * ldp + (size_t)t * BN + 4 * g4;
+#pragma unroll
+      for (int j = 0; j < FN; ++j) *(f32x4_t*)(p + w_rows(j)) = acc[i][j];
+    } else if constexpr (PAIRED) {
+#pragma unroll
+      for (int j = 0; j < FN / 2; ++j)
+        pol.store4(m, t, w_rows(j) + 4 * g4, BN, acc[i][j], acc[i][j + FN / 2]);
+    } else {
+#pragma unroll
+      for (int j = 0; j < FN; ++j) pol.store4_1(m, t * BN + w_rows(j) + 4 * g4, acc[i][j]);
+    }
   }
 }
 
@@ -814,6 +913,7 @@ static void launch_reduce(const Pol& pol, const float* part, int N, int M, int S
   const size_t total = (size_t)M * N / 8 / (Pol::PAIRED ? 2 : 1);
   const dim3 grid((unsigned)((total + 255) / 256)), block(256);
   if (S == 8) launch((splitk_reduce_kernel<BN, Pol, 8>), grid, block, 0, st, pol, part, N, M, S, ntiles);
+  else if (S == 3) launch((splitk_reduce_kernel<BN, Pol, 3>), grid, block, 0, st, pol, part, N, M, S, ntiles);
   else if (S == 4) launch((splitk_reduce_kernel<BN, Pol, 4>), grid, block, 0, st, pol, part, N, M, S, ntiles);
   else if (S == 2) launch((splitk_reduce_kernel<BN, Pol, 2>), grid, block, 0, st, pol, part, N, M, S, ntiles);
   else launch((splitk_reduce_kernel<BN, Pol, 0>), grid, block, 0, st, pol, part, N, M, S, ntiles);
@@ -841,42 +941,61 @@ static int gemm_krot() {
 
 // Split-K is only used while S * M stays small, which bounds the workspace.
 static constexpr int SPLIT_ROWS_MAX = 1024;
-// Row count from which the projections use gemm_big_kernel.
-static constexpr int BIG_ROWS_MIN = 512;
-
 size_t gemm_split_ws_floats(int M, int max_n) {
   (void)M;
   return (size_t)SPLIT_ROWS_MAX * max_n;
 }
 
+// Tiles of gemm_pp_kernel: rows, columns and the time of a K-step of 64 in a
+// full round of 256 workgroups (one per CU), in us.  A round of workgroups
+// takes steps * us + PP_FIXED_US (prologue, first copies, epilogue, launch).
+// Measured in a loop of 1024-2048 x 4096-8192 x 4096 products with random
+// operands: the 256 x 256 tile takes 2415 clocks for the 2048 clocks of MFMAs
+// that a K-step holds per SIMD, the smaller ones 1990 for 1536, 1600 and 1660
+// for 1024, 1410 for 768: each of the 4 barriers of a K-step costs about 45
+// clocks, and LDS reads outlast the MFMAs of small wave tiles.  With the
+// 256 x 256 tile the clock gives way too (1.6-1.8 GHz under this load, 2.1
+// with the copies left out).  A 128 x 128 tile with two workgroups per CU
+// (1510 clocks for 1024) was never the cheapest.
+struct PpTile {
+  int bm, bn;
+  float us;
+};
+static constexpr PpTile PP_TILES[] = {
+    {256, 256, 1.42f}, {256, 192, 1.07f}, {256, 128, 0.82f}, {128, 256, 0.84f}, {128, 192, 0.66f},
+};
+static constexpr int N_PP_TILES = sizeof(PP_TILES) / sizeof(PP_TILES[0]);
+static constexpr int PP_SLOTS = 256;
+static constexpr float PP_FIXED_US = 8.0f;
+// float32 partials of split-K are written once and read once
+static constexpr float PP_PARTIAL_BYTES_PER_US = 5.0e6f;
+static constexpr int PP_MAX_SPLIT = 4;
+
 // Per-projection launch choice: tile width BN (64, 96 or 128), split-K S
 // (0 = automatic) and the depth PW (4 or 8 K-steps) of the staging waves'
-// register ring of weight loads.
+// register ring of weight loads of gemm_bf16_kernel, with its row tile bm
+// (see launch_bf16_bm); or, with pp = 1 + an index into PP_TILES,
+// gemm_pp_kernel (-1: the tile and split that cost least).
 struct GemmCfg {
   int bn, s, pw;
-  int big = 0;
-  int bm = 128;   // row tile of gemm_bf16_kernel (see launch_bf16_bm)    // gemm_big_kernel tile: 1 = 256 x 128, 2 = 128 x 256 (8 waves, 2-stage ring),
-                  // 3 = 256 x 256 (16 waves, 3-stage ring), 4 = 128 x 256 (8 waves, 3-stage
-                  // ring), 5 = 256 x 256 (8 waves of 64 x 128, 3-stage ring), 6 = 256 x 128
-                  // (8 waves, 3-stage ring); 0 = gemm_bf16_kernel; -1 = automatic
+  int pp = 0;
+  int bm = 128;
 };
-static int big_rows(int big) { return big == 1 || big == 3 || big == 5 || big == 6 ? 256 : 128; }
-static int big_cols(int big) { return big == 1 || big == 6 ? 128 : 256; }
 
 // Tuning override, compiled only into a tuning build (SSM_TUNING defined):
-// SSM_GEMM_CFG="kind:bn:s:pw[:big[:bm]],..." with kind one of qkv, o, gate_up,
-// down, lm (big and bm as in GemmCfg); read once per process.  The product build
+// SSM_GEMM_CFG="kind:bn:s:pw[:pp[:bm]],..." with kind one of qkv, o, gate_up,
+// down, lm (pp and bm as in GemmCfg); read at every launch.  The product build
 // always takes the measured defaults.
 static GemmCfg cfg_override(const char* kind, GemmCfg c) {
 #ifdef SSM_TUNING
-  static const char* env = getenv("SSM_GEMM_CFG");
+  const char* env = getenv("SSM_GEMM_CFG");
   if (!env) return c;
   const size_t kl = strlen(kind);
   for (const char* p = env; p && *p;) {
     if (strncmp(p, kind, kl) == 0 && p[kl] == ':') {
-      int bn, s, pw, big = -1, bm = 128;
-      const int n = sscanf(p + kl + 1, "%d:%d:%d:%d:%d", &bn, &s, &pw, &big, &bm);
-      if (n >= 3) return GemmCfg{bn, s, pw, n >= 4 ? big : c.big, n == 5 ? bm : c.bm};
+      int bn, s, pw, pp = 0, bm = 128;
+      const int n = sscanf(p + kl + 1, "%d:%d:%d:%d:%d", &bn, &s, &pw, &pp, &bm);
+      if (n >= 3) return GemmCfg{bn, s, pw, n >= 4 ? pp : c.pp, n == 5 ? bm : c.bm};
     }
     p = strchr(p, ',');
     if (p) ++p;
@@ -896,21 +1015,32 @@ static int auto_split(int tiles, int M, int K, size_t ws_floats, int N) {
   return S;
 }
 
-// Split-K of the big tiles: the S in 1..4 (K a multiple of 256 S, partials
-// within the workspace) whose workgroups fill the CUs best over the rounds
-// they take; 2% of fill per extra split pays for the partials' traffic.
-// The 8-wave tiles with a 2-stage ring fit two workgroups per CU.
-static int big_split(int tiles, int big, int M, int K, int N, size_t ws_floats) {
-  const int slots = 256 * (big == 1 || big == 2 ? 2 : 1);
-  int best = 1;
-  double best_score = -1.0;
-  for (int S = 1; S <= 4; ++S) {
-    if (K % (256 * S) != 0 || (size_t)S * M * N > ws_floats) continue;
-    const long wgs = (long)tiles * S;
-    const double fill = (double)wgs / ((double)slots * ceil_div((int)wgs, slots));
-    const double score = fill - 0.02 * (S - 1);
-    if (score > best_score + 1e-9) { best_score = score; best = S; }
+// The tile (1 + its index) and split of gemm_pp_kernel that cost least by the
+// times above, among tiles that divide N and whose weight rows the policy can
+// map; 0 if there is none.  want > 0 / s > 0 fix the tile / the split.
+template <class Pol>
+static int pp_plan(const Pol& pol, int M, int K, int N, bool pair, size_t ws_floats,
+                   int (*bn_ok)(const Pol&, int), int want, int& s) {
+  int best = 0, best_s = 1;
+  float best_us = 0.f;
+  for (int i = 0; i < N_PP_TILES; ++i) {
+    const PpTile& p = PP_TILES[i];
+    if ((want > 0 && want != i + 1) || N % p.bn != 0 || !bn_ok(pol, p.bn)) continue;
+    const long tiles = (long)(N / p.bn) * ceil_div(M, p.bm);
+    for (int S = 1; S <= PP_MAX_SPLIT; ++S) {
+      if ((s > 0 && S != s) || S > K / 64 || (S > 1 && (size_t)S * M * N > ws_floats)) continue;
+      const float steps = (float)ceil_div(K / 64, S) * (pair ? 2 : 1);
+      const float rounds = (float)((tiles * S + PP_SLOTS - 1) / PP_SLOTS);
+      const float us = rounds * (steps * p.us + PP_FIXED_US) +
+                       (S > 1 ? 8.0f * S * M * N / PP_PARTIAL_BYTES_PER_US : 0.f);
+      if (!best || us < best_us) {
+        best = i + 1;
+        best_s = S;
+        best_us = us;
+      }
+    }
   }
+  s = best_s;
   return best;
 }
 
@@ -958,42 +1088,39 @@ static hipError_t launch_bf16_bm(const Pol& pol, const ActIn& a, int M, int K, i
 // Launch plan of one projection: the configuration with a valid tile width
 // and the split-K factor.
 template <class Pol>
-static GemmCfg plan_bf16(const char* kind, const Pol& pol, int M, int K, int N, GemmCfg c,
+static GemmCfg plan_bf16(const char* kind, const Pol& pol, int M, int K, int N, bool pair, GemmCfg c,
                          const SplitWs& ws, int (*bn_ok)(const Pol&, int)) {
   c = cfg_override(kind, c);
-  // many rows: the big-tile kernel where its shape constraints hold
-  if (c.big < 0) c.big = 0;
-  const int big_bn = c.big ? big_cols(c.big) : 128;
-  if (c.big && (M < BIG_ROWS_MIN || has_tile<Pol>::value || !bn_ok(pol, big_bn) ||
-                N % big_bn != 0 || K % 32 != 0))
-    c.big = 0;
-  if (c.big) c.bn = big_bn;
-  else if (c.bn > 128 || !bn_ok(pol, c.bn) || N % c.bn) c.bn = bn_ok(pol, 128) && N % 128 == 0 ? 128 : 64;
-  if (c.big || (c.bm != 64 && c.bm != 192 && c.bm != 256) || ((c.bm == 192 || c.bm == 256) && c.bn > 96))
+  if (c.pp != 0 && !has_tile<Pol>::value && K % 64 == 0) {
+    c.pp = pp_plan(pol, M, K, N, pair, ws.floats, bn_ok, c.pp, c.s);
+    if (c.pp) return c;
+  }
+  c.pp = 0;
+  if (c.bn > 128 || !bn_ok(pol, c.bn) || N % c.bn) c.bn = bn_ok(pol, 128) && N % 128 == 0 ? 128 : 64;
+  if ((c.bm != 64 && c.bm != 192 && c.bm != 256) || ((c.bm == 192 || c.bm == 256) && c.bn > 96))
     c.bm = 128;
-  const int tiles = (N / c.bn) * ceil_div(M, c.big ? big_rows(c.big) : c.bm);
-  int S = c.s > 0 ? c.s : c.big ? big_split(tiles, c.big, M, K, N, ws.floats)
-                                 : auto_split(tiles, M, K, ws.floats, N);
+  const int tiles = (N / c.bn) * ceil_div(M, c.bm);
+  int S = c.s > 0 ? c.s : auto_split(tiles, M, K, ws.floats, N);
   while (S > 1 && (K % (256 * S) != 0 || (size_t)S * M * N > ws.floats)) S /= 2;
   c.s = S;
   return c;
 }
 
-template <int BM, int BN, int WM, int WN, int NS, class Pol>
-static hipError_t launch_big(const Pol& pol, const ActIn& a, int M, int K, int N, int S,
-                             SplitWs ws, hipStream_t st, bool reduce) {
+template <int BM, int BN, int WM, int WN, class Pol>
+static hipError_t launch_pp(const Pol& pol, const ActIn& a, int M, int K, int N, int S,
+                            SplitWs ws, hipStream_t st, bool reduce) {
   if constexpr (has_tile<Pol>::value) {
-    return hipErrorInvalidValue;   // whole-tile epilogues run on gemm_bf16_kernel only
+    return hipErrorInvalidValue;
   } else {
     const int ntiles = N / BN, mt = ceil_div(M, BM);
-    const dim3 grid(ntiles * mt * S), block(64 * WM * WN);
+    const dim3 grid(ntiles * mt * S), block(512);
     float* pp = S > 1 ? ws.part : nullptr;
     if (a.lo)
-      launch((gemm_big_kernel<BM, BN, WM, WN, NS, true, Pol>), grid, block, 0, st, pol,
-             (const bf16_t*)a.hi, a.lo, a.G, M, K / S, mt, S, pp, N);
+      launch((gemm_pp_kernel<BM, BN, WM, WN, true, Pol>), grid, block, 0, st, pol,
+             (const bf16_t*)a.hi, a.lo, a.G, M, K / 64, mt, S, pp, N);
     else
-      launch((gemm_big_kernel<BM, BN, WM, WN, NS, false, Pol>), grid, block, 0, st, pol,
-             (const bf16_t*)a.hi, a.lo, a.G, M, K / S, mt, S, pp, N);
+      launch((gemm_pp_kernel<BM, BN, WM, WN, false, Pol>), grid, block, 0, st, pol,
+             (const bf16_t*)a.hi, a.lo, a.G, M, K / 64, mt, S, pp, N);
     if (S > 1 && reduce) launch_reduce<BN>(pol, ws.part, N, M, S, ntiles, st);
     return hipGetLastError();
   }
@@ -1002,12 +1129,14 @@ static hipError_t launch_big(const Pol& pol, const ActIn& a, int M, int K, int N
 template <class Pol>
 static hipError_t launch_plan(const Pol& pol, const ActIn& a, int M, int K, int N, GemmCfg c,
                               SplitWs ws, hipStream_t st, bool reduce = true) {
-  if (c.big == 1) return launch_big<256, 128, 4, 2, 2>(pol, a, M, K, N, c.s, ws, st, reduce);
-  if (c.big == 2) return launch_big<128, 256, 2, 4, 2>(pol, a, M, K, N, c.s, ws, st, reduce);
-  if (c.big == 3) return launch_big<256, 256, 4, 4, 3>(pol, a, M, K, N, c.s, ws, st, reduce);
-  if (c.big == 4) return launch_big<128, 256, 2, 4, 3>(pol, a, M, K, N, c.s, ws, st, reduce);
-  if (c.big == 5) return launch_big<256, 256, 4, 2, 3>(pol, a, M, K, N, c.s, ws, st, reduce);
-  if (c.big == 6) return launch_big<256, 128, 4, 2, 3>(pol, a, M, K, N, c.s, ws, st, reduce);
+  switch (c.pp) {   // 1 + the index in PP_TILES
+    case 1: return launch_pp<256, 256, 2, 4>(pol, a, M, K, N, c.s, ws, st, reduce);
+    case 2: return launch_pp<256, 192, 4, 2>(pol, a, M, K, N, c.s, ws, st, reduce);
+    case 3: return launch_pp<256, 128, 4, 2>(pol, a, M, K, N, c.s, ws, st, reduce);
+    case 4: return launch_pp<128, 256, 2, 4>(pol, a, M, K, N, c.s, ws, st, reduce);
+    case 5: return launch_pp<128, 192, 4, 2>(pol, a, M, K, N, c.s, ws, st, reduce);
+    default: break;
+  }
   if (c.bn == 96) return launch_bf16_bm<96>(pol, a, M, K, N, c.s, c.pw, c.bm, ws, st, reduce);
   if (c.bn == 64) return launch_bf16_bm<64>(pol, a, M, K, N, c.s, c.pw, c.bm, ws, st, reduce);
   return launch_bf16_bm<128>(pol, a, M, K, N, c.s, c.pw, c.bm, ws, st, reduce);
@@ -1016,7 +1145,7 @@ static hipError_t launch_plan(const Pol& pol, const ActIn& a, int M, int K, int 
 template <class Pol>
 static hipError_t run_bf16(const char* kind, Pol pol, const ActIn& a, int M, int K, int N,
                            GemmCfg c, SplitWs ws, hipStream_t st, int (*bn_ok)(const Pol&, int)) {
-  c = plan_bf16(kind, pol, M, K, N, c, ws, bn_ok);
+  c = plan_bf16(kind, pol, M, K, N, a.lo != nullptr, c, ws, bn_ok);
   return launch_plan(pol, a, M, K, N, c, ws, st);
 }
 
@@ -1099,61 +1228,46 @@ static hipError_t run_f32(const Pol& pol, const ActIn& a, int M, int K, int N, S
 }
 
 // Default launch choices: the cached-step row counts (M <= 256) are
-// HBM-bound and want every CU streaming weights; block-start row counts are
-// MFMA-bound and want wide tiles.  `paired`: the activations carry the lo part
-// (twice the MFMA work per operand byte, so the wide 3-stage tiles pay more).
-// Measured choices:
-//  * row tiles of gemm_bf16_kernel: 128 rows, except 256 for the one-pass QKV
-//    from 257 to 511 rows (two row tiles instead of three or four) and the
-//    one-pass gate/up from 129 to 256 rows (one row tile instead of two); 64-
-//    and 192-row tiles and the 256-row tiles elsewhere measured slower;
-//  * QKV: 96-column tiles below 512 rows (128 column tiles at d = 4096 with
-//    32 + 2 x 32 heads: with the automatic split-K, 2 ways up to 128 rows,
-//    256 workgroups where 128-column tiles left 64 CUs idle); 256 x 128 tiles
-//    from 512 rows with the pair (2-stage ring) and from 1024 rows in one pass
-//    (3-stage ring, 24 KB per stage: two workgroups per CU; below 1024 rows
-//    its 256-row tiles leave slots empty).  256-column tiles (two heads) took
-//    longer at 1776 rows: 336 tiles leave most of a second round empty;
-//  * gate/up: 96-column tiles below 512 rows (one workgroup per CU at
-//    2F = 24576; the planner falls back to 128 where 96 does not divide 2F);
-//    from 512 rows 128 x 256 with the pair and the 3-stage 256 x 128 tiles
-//    in one pass, from 1024 rows 256 x 256 with 16 waves and a 3-stage ring
-//    (half the operand bytes per MFMA, two K-steps of copy latency hidden);
-//  * O / down (N = d): gemm_bf16_kernel, whose 128-row tiles fill more CUs;
-//    from 1024 rows the 256 x 256 tiles with split-K chosen for CU fill
-//    (big_split; its partials go through the fused sum + RMSNorm).  Up to
-//    128 rows O takes 64-column tiles and split-K 4, which halves the float32
-//    partials of the 8-way split.
+// HBM-bound and want every CU streaming weights; more rows are MFMA-bound and
+// take gemm_pp_kernel.  `paired`: the activations carry the lo part (twice the
+// MFMA work per weight byte).  Measured choices (8B shape, us per layer over
+// the four projections with their sums, gemm_bf16_kernel / gemm_pp_kernel):
+//  * gemm_pp_kernel from 257 rows in one pass (240 rows 173 / 197, 300 rows 234 /
+//    225, 376 rows 245 / 225, 504 rows 279 / 238), from 385 rows with the pair
+//    (300 rows 353 / 381, 376 rows 393 / 387, 440 rows 423 / 403, 504 rows 464 /
+//    414);
+//  * row tiles of gemm_bf16_kernel: 128 rows, except 256 for the one-pass
+//    gate/up from 129 rows (one row tile instead of two); 64- and 192-row
+//    tiles and the 256-row tiles elsewhere measured slower;
+//  * QKV: 96-column tiles (128 column tiles at d = 4096 with 32 + 2 x 32 heads:
+//    with the automatic split-K, 2 ways up to 128 rows, 256 workgroups where
+//    128-column tiles left 64 CUs idle);
+//  * gate/up: 96-column tiles (one workgroup per CU at 2F = 24576; the planner
+//    falls back to 128 where 96 does not divide 2F);
+//  * O / down (N = d): 128-column tiles with split-K; up to 128 rows O takes
+//    64-column tiles and split-K 4, which halves the float32 partials of the
+//    8-way split.
 static GemmCfg default_cfg(const char* kind, int M, bool paired) {
-  const bool small = M <= 256;
-  if (!strcmp(kind, "qkv")) {
-    if (M < 512) {
-      GemmCfg c{96, 0, 4, 0};
-      if (!paired && M > 256) c.bm = 256;   // two 256-row tiles: 7-17% faster at 376-504 rows
-      return c;
-    }
-    return GemmCfg{128, 1, 3, paired ? 1 : (M >= 1024 ? 6 : 0)};
-  }
-  if (!strcmp(kind, "gate_up")) {
-    if (M < 512) {
-      GemmCfg c{96, 1, 4, 0};
-      if (!paired && M > 128 && M <= 256) c.bm = 256;   // one row tile: 9% faster at 240 rows
-      return c;
-    }
-    return GemmCfg{128, 1, 3, M >= 1024 ? 3 : (paired ? 2 : 6)};
-  }
   if (!strcmp(kind, "lm")) return GemmCfg{128, 1, 4, 0};
+  if (M > (paired ? 384 : 256)) return GemmCfg{128, 0, 4, -1};
+  if (!strcmp(kind, "qkv")) return GemmCfg{96, 0, 4, 0};
+  if (!strcmp(kind, "gate_up")) {
+    GemmCfg c{96, 1, 4, 0};
+    if (!paired && M > 128) c.bm = 256;   // one row tile: 9% faster at 240 rows
+    return c;
+  }
   if (!strcmp(kind, "o") && M <= 128) return GemmCfg{64, 4, 4, 0};
-  return small ? GemmCfg{128, 0, 4, 0} : GemmCfg{128, 0, 3, M >= 1024 ? 3 : 0};
+  return GemmCfg{128, 0, 4, 0};
 }
 
-// tile widths: 64, 96 and 128 (gemm_bf16_kernel), 128 and 256 (gemm_big_kernel)
-template <class Pol> static int any_bn(const Pol&, int bn) { return bn == 64 || bn == 96 || bn == 128 || bn == 256; }
+// tile widths: 64, 96 and 128 (gemm_bf16_kernel), 128, 192 and 256 (gemm_pp_kernel)
+template <class Pol> static int any_bn(const Pol&, int bn) {
+  return bn == 64 || bn == 96 || bn == 128 || bn == 192 || bn == 256;
+}
 // any width whose tiles divide the heads' concatenated halves (the epilogue's
 // 8-column groups then never straddle a head)
 static int qkv_bn(const PolQKV<bf16_t, f16_t>& p, int bn) {
-  return (bn == 64 || bn == 96 || bn == 128 || bn == 256) && ((p.H + 2 * p.Hkv) * p.dh) % bn == 0 &&
-         (p.dh / 2) % 8 == 0;
+  return any_bn(p, bn) && ((p.H + 2 * p.Hkv) * p.dh) % bn == 0 && (p.dh / 2) % 8 == 0;
 }
 
 hipError_t gemm_qkv(int dtype, const ActIn& a, int M, int d, const void* wq, const void* wk,
@@ -1180,7 +1294,8 @@ hipError_t gemm_resid(int dtype, const char* kind, const ActIn& a, int M, int K,
     e = run_f32(p, a, M, K, N, ws, st);
   } else {
     PolResid<bf16_t> p{(const bf16_t*)w, K, N, resid};
-    const GemmCfg c = plan_bf16(kind, p, M, K, N, default_cfg(kind, M, a.lo != nullptr), ws,
+    const GemmCfg c = plan_bf16(kind, p, M, K, N, a.lo != nullptr,
+                                default_cfg(kind, M, a.lo != nullptr), ws,
                                 any_bn<PolResid<bf16_t>>);
     const int nc = ceil_div(N / 8, 512);
     const bool fuse = nrm && c.s > 1 && N % 8 == 0 && nc <= 2 && ((uintptr_t)nrm->g & 15) == 0;
@@ -1188,6 +1303,7 @@ hipError_t gemm_resid(int dtype, const char* kind, const ActIn& a, int M, int K,
     if (e != hipSuccess || !fuse) goto separate;
     if (c.s == 8) launch_resid_norm<8>(nc, c.s, M, N, ws.part, resid, nrm, st);
     else if (c.s == 4) launch_resid_norm<4>(nc, c.s, M, N, ws.part, resid, nrm, st);
+    else if (c.s == 3) launch_resid_norm<3>(nc, c.s, M, N, ws.part, resid, nrm, st);
     else if (c.s == 2) launch_resid_norm<2>(nc, c.s, M, N, ws.part, resid, nrm, st);
     else launch_resid_norm<0>(nc, c.s, M, N, ws.part, resid, nrm, st);
     return hipGetLastError();

@@ -186,6 +186,18 @@ struct ActOut {
       if (lo) lo[i] = f2bf(v - bf2f(h));
     }
   }
+  // columns k .. k + 3 of row m, k a multiple of 4: half a chunk of the
+  // fragment order (bfloat16 operands only)
+  __device__ __forceinline__ void store4(int m, int k, const float (&v)[4]) const {
+    const size_t i = frag_index(m, k, G);
+    const uint2 h = {pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+    *(uint2*)((bf16_t*)hi + i) = h;
+    if (lo) {
+      const uint2 l = {pack_bf16x2(v[0] - __uint_as_float(h.x << 16), v[1] - __uint_as_float(h.x & 0xffff0000u)),
+                       pack_bf16x2(v[2] - __uint_as_float(h.y << 16), v[3] - __uint_as_float(h.y & 0xffff0000u))};
+      *(uint2*)(lo + i) = l;
+    }
+  }
   // columns k .. k + 7 of row m, k a multiple of 8: one chunk of the fragment
   // order, so one 16-byte store per part
   template <typename T>
