@@ -1160,7 +1160,7 @@ __global__ void __launch_bounds__(512) resid_norm_kernel(const float* __restrict
                                                          const bf16_t* __restrict__ g, float eps,
                                                          ActOut y) {
   __shared__ float red[8];
-  const int m = blockIdx.x, tid = threadIdx.x, nc8 = N >> 3;
+  const int m = xcd_row(blockIdx.x, gridDim.x), tid = threadIdx.x, nc8 = N >> 3;
   float v[NC][8];
   float ss = 0.f;
 #pragma unroll

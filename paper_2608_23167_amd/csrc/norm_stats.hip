@@ -25,7 +25,7 @@ __global__ void __launch_bounds__(256) norm_vec_kernel(const float* __restrict__
                                                        const T* __restrict__ g, float eps,
                                                        ActOut y, int per, int stride, int off) {
   __shared__ float red[4];
-  const int o = blockIdx.x, tid = threadIdx.x;
+  const int o = xcd_row(blockIdx.x, gridDim.x), tid = threadIdx.x;
   const int nv4 = d >> 2;
   const float4* xr = (const float4*)(x + ((size_t)(o / per) * stride + off + o % per) * d);
   float4 v[NV], gv[NV];
