@@ -42,6 +42,7 @@
 #include <type_traits>
 
 #include "internal.h"
+#include "row_stats.h"
 
 namespace ssm {
 
@@ -247,30 +248,49 @@ struct PolStore {
   }
 };
 
-// LM head: per-row partial softmax statistics of every half tile (64 vocab
-// columns): running max, sum of exp(x - max) and the 8 largest logits with
-// their ids, [MASK] excluded; optionally the logits themselves.
-struct LMPartial {
-  float m, s;
-  float v[8];
-  int id[8];
+// LM head: per-row partial softmax statistics of every 64 vocabulary columns
+// (a segment): running max, sum of exp(x - max) and the 8 largest logits with
+// their ids, best first, [MASK] excluded; optionally the logits themselves.
+// The part that every merge reads lies apart from the rest of the list.
+struct LMHead {
+  float m, s, v0;
+  int id0;
+};
+struct LMTail {
+  float v[7];
+  int id[7];
+};
+struct LMParts {
+  LMHead* head;        // [M][n_part]
+  LMTail* tail;        // [M][n_part]
+  int n_part;          // N / 64
 };
 
-__device__ __forceinline__ bool stat_better(float v, int i, float w, int j) {
-  return v > w || (v == w && i < j);
+// Compare-exchange and top-8 networks on float64 keys: v_max_f64 / v_min_f64
+// move a value and its column together, with no branch.
+__device__ __forceinline__ void key_ce(double& a, double& b) {
+  const double x = __builtin_fmax(a, b), y = __builtin_fmin(a, b);
+  a = x;
+  b = y;
 }
-
-__device__ __forceinline__ void stat_insert(float (&tv)[8], int (&ti)[8], float v, int i) {
+// sorts 8 keys, largest first (odd-even merge sort, 19 exchanges)
+__device__ __forceinline__ void key_sort8(double (&a)[8]) {
+  key_ce(a[0], a[1]); key_ce(a[2], a[3]); key_ce(a[4], a[5]); key_ce(a[6], a[7]);
+  key_ce(a[0], a[2]); key_ce(a[1], a[3]); key_ce(a[4], a[6]); key_ce(a[5], a[7]);
+  key_ce(a[1], a[2]); key_ce(a[5], a[6]);
+  key_ce(a[0], a[4]); key_ce(a[1], a[5]); key_ce(a[2], a[6]); key_ce(a[3], a[7]);
+  key_ce(a[2], a[4]); key_ce(a[3], a[5]);
+  key_ce(a[1], a[2]); key_ce(a[3], a[4]); key_ce(a[5], a[6]);
+}
+// the 8 largest of two sorted lists, sorted (bitonic merge, 12 exchanges)
+__device__ __forceinline__ void key_merge8(double (&a)[8], const double (&b)[8]) {
 #pragma unroll
-  for (int q = 0; q < 8; ++q) {
-    const bool gt = stat_better(v, i, tv[q], ti[q]);
-    const float ov = tv[q];
-    const int oi = ti[q];
-    tv[q] = gt ? v : ov;
-    ti[q] = gt ? i : oi;
-    v = gt ? ov : v;
-    i = gt ? oi : i;
-  }
+  for (int i = 0; i < 8; ++i) a[i] = __builtin_fmax(a[i], b[7 - i]);
+#pragma unroll
+  for (int d = 4; d > 0; d >>= 1)
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      if (!(i & d)) key_ce(a[i], a[i + d]);
 }
 
 template <typename T>
@@ -279,14 +299,20 @@ struct PolLMStats {
   static constexpr bool TILE = true;
   const T* w;
   int ldb, N, mask_id;
-  LMPartial* part;     // [M][2 * ntiles]
-  int n_part;          // 2 * ntiles
+  LMParts part;
   float* logits;       // optional [M][ldc]
   int ldc;
   __device__ __forceinline__ void b_ptrs(int t, int BN, const T*& lo, const T*& hi) const {
     lo = w + (size_t)t * BN * ldb;
     hi = lo + (size_t)(BN / 2) * ldb;
   }
+  // One thread per (row, segment).  Per segment: the top 8 of 64 keys by sorting
+  // networks over batches of 8, then the sum of exponentials against the
+  // maximum just found.  A key is 64 times the ordered bits of the value plus
+  // 63 - column, an integer that float64 holds exactly; NaN and [MASK] are
+  // below every value.  (A sorted insertion per value runs nearly all of its 8
+  // steps for some lane of the wave: the 120-row head of 126464 ids took 229 us
+  // with it, 218 with the networks; at 480 rows on gemm_pp_kernel 627 and 494.)
   template <int BM, int BN, int CS>
   __device__ __forceinline__ void tile(const float* Cs, int m0, int M, int t) const {
     const int tid = threadIdx.x;
@@ -296,29 +322,48 @@ struct PolLMStats {
         if (m0 + r < M) logits[(size_t)(m0 + r) * ldc + (size_t)t * BN + c] = Cs[r * CS + c];
       }
     }
-    // thread -> (row, half): 2 threads per row, each over BN / 2 columns
-    for (int idx = tid; idx < BM * 2; idx += blockDim.x) {
-      const int r = idx >> 1, h = idx & 1;
+    constexpr double NONE = -1.0e18;
+    for (int idx = tid; idx < BM * (BN / 64); idx += blockDim.x) {
+      const int r = idx % BM, h = idx / BM;          // rows fastest
       if (m0 + r >= M) continue;
+      const float* x = Cs + r * CS + 64 * h;
+      const int id_base = t * BN + 64 * h, masked = mask_id - id_base;
+      double top[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) top[q] = NONE;
+      for (int c0 = 0; c0 < 64; c0 += 8) {
+        double b[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const float v = x[c0 + e];
+          const double key = fma((double)ordered_bits(v), 64.0, (double)(63 - c0 - e));
+          b[e] = (v == v && c0 + e != masked) ? key : NONE;
+        }
+        key_sort8(b);
+        key_merge8(top, b);
+      }
       float tv[8];
       int ti[8];
 #pragma unroll
-      for (int q = 0; q < 8; ++q) { tv[q] = -INFINITY; ti[q] = 0x7fffffff; }
-      float mx = -INFINITY, sm = 0.f;
-      const int c0 = h * (BN / 2);
-      for (int c = c0; c < c0 + BN / 2; ++c) {
-        const int v = t * BN + c;
-        if (v == mask_id) continue;
-        const float x = Cs[r * CS + c];
-        if (x > mx) { sm = sm * expf(mx - x) + 1.0f; mx = x; }
-        else sm += expf(x - mx);
-        if (stat_better(x, v, tv[7], ti[7])) stat_insert(tv, ti, x, v);
+      for (int q = 0; q < 8; ++q) {
+        const long long kq = (long long)top[q];
+        const bool none = top[q] == NONE;
+        tv[q] = none ? -INFINITY : ordered_float((int)(kq >> 6));
+        ti[q] = none ? STAT_NONE : id_base + 63 - (int)(kq & 63);
       }
-      LMPartial* o = part + (size_t)(m0 + r) * n_part + 2 * t + h;
-      o->m = mx;
-      o->s = sm;
+      // the best column counts as 1 (exp(inf - inf) is not)
+      const float mx = tv[0];
+      const int best = ti[0] - id_base;
+      float sm = 0.f;
+#pragma unroll 8
+      for (int c = 0; c < 64; ++c)
+        if (c != masked) sm += c == best ? 1.0f : expf(x[c] - mx);
+      const size_t o = (size_t)(m0 + r) * part.n_part + (BN / 64) * t + h;
+      *(float4*)(part.head + o) = make_float4(mx, sm, tv[0], __int_as_float(ti[0]));
+      LMTail l;
 #pragma unroll
-      for (int q = 0; q < 8; ++q) { o->v[q] = tv[q]; o->id[q] = ti[q]; }
+      for (int q = 1; q < 8; ++q) { l.v[q - 1] = tv[q]; l.id[q - 1] = ti[q]; }
+      part.tail[o] = l;
     }
   }
 };
@@ -672,7 +717,11 @@ __global__ void __launch_bounds__(512, 2) gemm_pp_kernel(Pol pol, const bf16_t* 
   static_assert(BM % 128 == 0 && BN % 64 == 0, "whole copies per wave");
   constexpr int A_HALF = BM * 64, A_STAGE = 2 * A_HALF, W_STAGE = BN * 128;   // bytes
   constexpr int INFLIGHT = LW + 2 * LA;
-  __shared__ __attribute__((aligned(1024))) char smem[2 * A_STAGE + 3 * W_STAGE];
+  // policies that look at a whole tile get it in LDS, EB rows at a time
+  constexpr bool TILE = has_tile<Pol>::value;
+  constexpr int EB = 128, CS = BN + 1, SMEM_W = 2 * A_STAGE + 3 * W_STAGE, SMEM_C = TILE ? EB * CS * 4 : 0;
+  static_assert(!TILE || EB % RW == 0, "a wave's rows in one chunk");
+  __shared__ __attribute__((aligned(1024))) char smem[SMEM_W > SMEM_C ? SMEM_W : SMEM_C];
   char* const Ws = smem + 2 * A_STAGE;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -798,6 +847,25 @@ __global__ void __launch_bounds__(512, 2) gemm_pp_kernel(Pol pol, const bf16_t* 
   if (!late) pp_barrier();
   wait_vmcnt<0>();                                  // no copy lands after the workgroup ends
 
+  if constexpr (TILE) {
+    float* Cs = (float*)smem;
+#pragma unroll
+    for (int h = 0; h < BM / EB; ++h) {
+      __syncthreads();                              // the ring, or the chunk before, is done with
+      if (RW * wm / EB == h) {
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+          for (int j = 0; j < FN; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+              Cs[(RW * wm - EB * h + 16 * i + r16) * CS + w_rows(j) + 4 * g4 + r] = acc[i][j][r];
+      }
+      __syncthreads();
+      pol.template tile<EB, BN, CS>(Cs, m0 + EB * h, M, t);
+    }
+    return;
+  } else {
   // acc[i][j][r] = C[RW wm + 16 i + lane % 16][w_rows(j) + 4 (lane / 16) + r]
 #pragma unroll
   for (int i = 0; i < FM; ++i) {
@@ -815,6 +883,7 @@ __global__ void __launch_bounds__(512, 2) gemm_pp_kernel(Pol pol, const bf16_t* 
 #pragma unroll
       for (int j = 0; j < FN; ++j) pol.store4_1(m, t * BN + w_rows(j) + 4 * g4, acc[i][j]);
     }
+  }
   }
 }
 
@@ -1015,6 +1084,15 @@ static int auto_split(int tiles, int M, int K, size_t ws_floats, int N) {
   return S;
 }
 
+// Time of gemm_pp_kernel with tile number `tile` (1 + its index) and split S, in us.
+static float pp_cost(int tile, int M, int K, int N, bool pair, int S = 1) {
+  const PpTile& p = PP_TILES[tile - 1];
+  const long wgs = (long)(N / p.bn) * ceil_div(M, p.bm) * S;
+  const float steps = (float)ceil_div(K / 64, S) * (pair ? 2 : 1);
+  return (float)((wgs + PP_SLOTS - 1) / PP_SLOTS) * (steps * p.us + PP_FIXED_US) +
+         (S > 1 ? 8.0f * S * M * N / PP_PARTIAL_BYTES_PER_US : 0.f);
+}
+
 // The tile (1 + its index) and split of gemm_pp_kernel that cost least by the
 // times above, among tiles that divide N and whose weight rows the policy can
 // map; 0 if there is none.  want > 0 / s > 0 fix the tile / the split.
@@ -1026,13 +1104,9 @@ static int pp_plan(const Pol& pol, int M, int K, int N, bool pair, size_t ws_flo
   for (int i = 0; i < N_PP_TILES; ++i) {
     const PpTile& p = PP_TILES[i];
     if ((want > 0 && want != i + 1) || N % p.bn != 0 || !bn_ok(pol, p.bn)) continue;
-    const long tiles = (long)(N / p.bn) * ceil_div(M, p.bm);
     for (int S = 1; S <= PP_MAX_SPLIT; ++S) {
       if ((s > 0 && S != s) || S > K / 64 || (S > 1 && (size_t)S * M * N > ws_floats)) continue;
-      const float steps = (float)ceil_div(K / 64, S) * (pair ? 2 : 1);
-      const float rounds = (float)((tiles * S + PP_SLOTS - 1) / PP_SLOTS);
-      const float us = rounds * (steps * p.us + PP_FIXED_US) +
-                       (S > 1 ? 8.0f * S * M * N / PP_PARTIAL_BYTES_PER_US : 0.f);
+      const float us = pp_cost(i + 1, M, K, N, pair, S);
       if (!best || us < best_us) {
         best = i + 1;
         best_s = S;
@@ -1109,21 +1183,19 @@ static GemmCfg plan_bf16(const char* kind, const Pol& pol, int M, int K, int N, 
 template <int BM, int BN, int WM, int WN, class Pol>
 static hipError_t launch_pp(const Pol& pol, const ActIn& a, int M, int K, int N, int S,
                             SplitWs ws, hipStream_t st, bool reduce) {
-  if constexpr (has_tile<Pol>::value) {
-    return hipErrorInvalidValue;
-  } else {
-    const int ntiles = N / BN, mt = ceil_div(M, BM);
-    const dim3 grid(ntiles * mt * S), block(512);
-    float* pp = S > 1 ? ws.part : nullptr;
-    if (a.lo)
-      launch((gemm_pp_kernel<BM, BN, WM, WN, true, Pol>), grid, block, 0, st, pol,
-             (const bf16_t*)a.hi, a.lo, a.G, M, K / 64, mt, S, pp, N);
-    else
-      launch((gemm_pp_kernel<BM, BN, WM, WN, false, Pol>), grid, block, 0, st, pol,
-             (const bf16_t*)a.hi, a.lo, a.G, M, K / 64, mt, S, pp, N);
+  const int ntiles = N / BN, mt = ceil_div(M, BM);
+  const dim3 grid(ntiles * mt * S), block(512);
+  float* pp = S > 1 ? ws.part : nullptr;
+  if (a.lo)
+    launch((gemm_pp_kernel<BM, BN, WM, WN, true, Pol>), grid, block, 0, st, pol,
+           (const bf16_t*)a.hi, a.lo, a.G, M, K / 64, mt, S, pp, N);
+  else
+    launch((gemm_pp_kernel<BM, BN, WM, WN, false, Pol>), grid, block, 0, st, pol,
+           (const bf16_t*)a.hi, a.lo, a.G, M, K / 64, mt, S, pp, N);
+  if constexpr (!has_tile<Pol>::value) {   // whole-tile epilogues never split K
     if (S > 1 && reduce) launch_reduce<BN>(pol, ws.part, N, M, S, ntiles, st);
-    return hipGetLastError();
   }
+  return hipGetLastError();
 }
 
 template <class Pol>
@@ -1244,11 +1316,15 @@ static hipError_t run_f32(const Pol& pol, const ActIn& a, int M, int K, int N, S
 //    128-column tiles left 64 CUs idle);
 //  * gate/up: 96-column tiles (one workgroup per CU at 2F = 24576; the planner
 //    falls back to 128 where 96 does not divide 2F);
+//  * LM head: gemm_pp_kernel on 256-column tiles from 129 rows (126464 ids: 120
+//    rows 218 / 211, 240 rows 370 / 297, 480 rows 651 / 494; 152064 ids: 120 rows
+//    249 / 268, 240 rows 407 / 358), which halves the activation reads per weight
+//    read; below that the smaller tiles' last round is fuller;
 //  * O / down (N = d): 128-column tiles with split-K; up to 128 rows O takes
 //    64-column tiles and split-K 4, which halves the float32 partials of the
 //    8-way split.
 static GemmCfg default_cfg(const char* kind, int M, bool paired) {
-  if (!strcmp(kind, "lm")) return GemmCfg{128, 1, 4, 0};
+  if (!strcmp(kind, "lm")) return GemmCfg{128, 1, 4, M > 128 ? -1 : 0};
   if (M > (paired ? 384 : 256)) return GemmCfg{128, 0, 4, -1};
   if (!strcmp(kind, "qkv")) return GemmCfg{96, 0, 4, 0};
   if (!strcmp(kind, "gate_up")) {
@@ -1331,121 +1407,78 @@ hipError_t gemm_store_f32(const ActIn& a, int M, int K, const void* w, int N, fl
 }
 
 // Merges the partial statistics of one row (one workgroup per row), in a
-// fixed order: deterministic.
-__global__ void __launch_bounds__(256) lm_merge_kernel(const LMPartial* __restrict__ part,
-                                                       int n_part, int k,
+// fixed order: deterministic.  120 rows of 1976 segments: 30 us with a list
+// kept per thread and 8 block-wide searches, 20 us with row_stats_end.
+__global__ void __launch_bounds__(256) lm_merge_kernel(LMParts part, int k,
                                                        int32_t* __restrict__ argmax,
                                                        float* __restrict__ conf,
                                                        int32_t* __restrict__ topk_ids,
                                                        float* __restrict__ topk_w) {
-  __shared__ float s_m[4];
-  __shared__ float s_s[4];
-  __shared__ float s_v[4];
-  __shared__ int s_i[4];
-  const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const LMPartial* P = part + (size_t)row * n_part;
-  float tv[8];
-  int ti[8];
+  __shared__ RowStatShared sh;
+  const int row = blockIdx.x, tid = threadIdx.x, n = part.n_part;
+  const float4* H = (const float4*)part.head + (size_t)row * n;
+  const LMTail* L = part.tail + (size_t)row * n;
+  float m = -INFINITY, s = 0.f, v = -INFINITY;
+  int i = STAT_NONE;
+  // this thread's segments j = tid + 256 c, in that order, CH loaded at a time
+  constexpr int CH = 8;
+  for (int j0 = tid; j0 < n; j0 += 256 * CH) {
+    float4 h[CH];
 #pragma unroll
-  for (int q = 0; q < 8; ++q) { tv[q] = -INFINITY; ti[q] = 0x7fffffff; }
-  float mx = -INFINITY, sm = 0.f;
-  // this thread's partials j = tid + 256 i, in that order; CH of them are
-  // loaded before any is folded in, so a row costs a few round trips
-  constexpr int CH = 4;
-  for (int j0 = tid; j0 < n_part; j0 += 256 * CH) {
-    LMPartial buf[CH];
-#pragma unroll
-    for (int c = 0; c < CH; ++c)
-      if (j0 + 256 * c < n_part) buf[c] = P[j0 + 256 * c];
+    for (int c = 0; c < CH; ++c) h[c] = H[min(j0 + 256 * c, n - 1)];
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
-      if (j0 + 256 * c >= n_part) break;
-      const LMPartial& p = buf[c];
-      if (p.s > 0.f) {
-        if (p.m > mx) { sm = sm * expf(mx - p.m) + p.s; mx = p.m; }
-        else sm += p.s * expf(p.m - mx);
+      if (j0 + 256 * c >= n) break;
+      if (h[c].y > 0.f) {
+        if (h[c].x > m) { s = s * expf(m - h[c].x) + h[c].y; m = h[c].x; }
+        else s += h[c].y * expf(h[c].x - m);
       }
-      // a partial's values are sorted best first: stop at the first one that
-      // does not enter this thread's list
-      for (int q = 0; q < 8; ++q) {
-        if (!stat_better(p.v[q], p.id[q], tv[7], ti[7])) break;
-        stat_insert(tv, ti, p.v[q], p.id[q]);
-      }
+      if (stat_better(h[c].z, __float_as_int(h[c].w), v, i)) { v = h[c].z; i = __float_as_int(h[c].w); }
     }
   }
-  // (max, sum) pairs over the workgroup: a butterfly within each wave (both
-  // partners compute the same sum, in either order), then the 4 waves in order
-  auto combine = [](float& m, float& s, float om, float os) {
-    if (!(os > 0.f)) return;
-    if (!(s > 0.f)) { m = om; s = os; return; }
-    const float M = fmaxf(m, om);
-    s = s * expf(m - M) + os * expf(om - M);
-    m = M;
-  };
+  row_stats_end(sh, m, s, v, i, row, k, argmax, conf, topk_ids, topk_w,
+                [&](float (&tv)[STAT_K], int (&ti)[STAT_K], float fv, int fi) {
+    for (int j0 = tid; j0 < n; j0 += 256 * CH) {
+      float4 h[CH];
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const float om = __shfl_xor(mx, o, 64), os = __shfl_xor(sm, o, 64);
-    combine(mx, sm, om, os);
-  }
-  if (lane == 0) { s_m[wave] = mx; s_s[wave] = sm; }
-  __syncthreads();
-  float M = s_m[0], S = s_s[0];
-  for (int w = 1; w < 4; ++w) combine(M, S, s_m[w], s_s[w]);
-  float best_v[8];
-  int best_i[8];
-  for (int q = 0; q < 8; ++q) {
-    float v = tv[0];
-    int i = ti[0];
+      for (int c = 0; c < CH; ++c) h[c] = H[min(j0 + 256 * c, n - 1)];
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      const float ov = __shfl_xor(v, o, 64);
-      const int oi = __shfl_xor(i, o, 64);
-      if (stat_better(ov, oi, v, i)) { v = ov; i = oi; }
-    }
-    __syncthreads();
-    if (lane == 0) { s_v[wave] = v; s_i[wave] = i; }
-    __syncthreads();
-    v = s_v[0];
-    i = s_i[0];
-    for (int w = 1; w < 4; ++w)
-      if (stat_better(s_v[w], s_i[w], v, i)) { v = s_v[w]; i = s_i[w]; }
-    best_v[q] = v;
-    best_i[q] = i;
-    if (ti[0] == i && tv[0] == v) {   // the owner pops its head (ids are unique)
+      for (int c = 0; c < CH; ++c) {
+        const int j = j0 + 256 * c, id0 = __float_as_int(h[c].w);
+        if (j >= n || stat_better(fv, fi, h[c].z, id0)) continue;
+        stat_insert(tv, ti, h[c].z, id0);
+        const LMTail l = L[j];
 #pragma unroll
-      for (int t = 0; t < 7; ++t) { tv[t] = tv[t + 1]; ti[t] = ti[t + 1]; }
-      tv[7] = -INFINITY;
-      ti[7] = 0x7fffffff;
-    }
-  }
-  if (tid == 0) {
-    argmax[row] = best_i[0];
-    conf[row] = 1.0f / S;   // exp(max - max) / sum exp(x - max)
-    float z = 0.f;
-    for (int q = 0; q < 8; ++q)
-      if (q < k) z += expf(best_v[q] - best_v[0]);
-    for (int q = 0; q < 8; ++q)
-      if (q < k) {
-        topk_ids[(size_t)row * k + q] = best_i[q];
-        topk_w[(size_t)row * k + q] = expf(best_v[q] - best_v[0]) / z;
+        for (int q = 0; q < 7; ++q)
+          if (!stat_better(fv, fi, l.v[q], l.id[q])) stat_insert(tv, ti, l.v[q], l.id[q]);
       }
-  }
+    }
+  });
 }
 
-size_t lm_stats_ws_bytes(int M, int N) { return (size_t)M * (2 * (N / 128)) * sizeof(LMPartial); }
+size_t lm_stats_ws_bytes(int M, int N) {
+  return (size_t)M * (N / 64) * (sizeof(LMHead) + sizeof(LMTail));
+}
 
 hipError_t lm_head_stats(const ActIn& a, int M, int K, const void* w, int N, int mask_id, int k,
                          void* stats_ws, float* logits, int32_t* argmax, float* conf,
                          int32_t* topk_ids, float* topk_w, hipStream_t st) {
-  constexpr int BN = 128;
-  const int ntiles = N / BN;
-  PolLMStats<bf16_t> p{(const bf16_t*)w, K, N, mask_id, (LMPartial*)stats_ws, 2 * ntiles, logits, N};
+  LMParts parts{(LMHead*)stats_ws, (LMTail*)((LMHead*)stats_ws + (size_t)M * (N / 64)), N / 64};
+  PolLMStats<bf16_t> p{(const bf16_t*)w, K, N, mask_id, parts, logits, N};
   const GemmCfg c = cfg_override("lm", default_cfg("lm", M, a.lo != nullptr));
-  SplitWs none{nullptr, 0};
-  hipError_t e = launch_bf16_pw<128, BN>(p, a, M, K, N, 1, c.pw, none, st, true);
+  const SplitWs none{nullptr, 0};
+  hipError_t e;
+  if (c.pp && N % 256 == 0) {
+    // one or two groups of 128 rows per tile, whichever takes less time
+    const bool pair = a.lo != nullptr;
+    e = pp_cost(1, M, K, N, pair) < pp_cost(4, M, K, N, pair)
+            ? launch_pp<256, 256, 2, 4>(p, a, M, K, N, 1, none, st, false)
+            : launch_pp<128, 256, 2, 4>(p, a, M, K, N, 1, none, st, false);
+  } else {
+    e = launch_bf16_pw<128, 128>(p, a, M, K, N, 1, c.pw, none, st, true);
+  }
   if (e != hipSuccess) return e;
-  launch(lm_merge_kernel, dim3(M), dim3(256), 0, st, (const LMPartial*)stats_ws,
-                     2 * ntiles, k, argmax, conf, topk_ids, topk_w);
+  launch(lm_merge_kernel, dim3(M), dim3(256), 0, st, parts, k, argmax, conf, topk_ids, topk_w);
   return hipGetLastError();
 }
 

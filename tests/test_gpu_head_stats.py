@@ -1,0 +1,63 @@
+"""Row statistics of the LM head against the logits of the same call: ids in
+order (larger logit, then lower id), confidence and renormalised weights, at the
+edges of the row tiles, for vocabularies that do and do not divide into the
+column tiles, with ties within and across the 64-column segments.
+"""
+import dataclasses
+
+import pytest
+import torch
+
+from synthetic import LLADA_8B, TINY, make_weights, seeded_normal
+
+pytestmark = pytest.mark.gpu
+
+
+def _head(base, rows, vocab, k, mask_id):
+    """(logits, argmax, conf, ids, weights) of a model without layers."""
+    from paper_2608_23167_amd import _lib as L
+    from paper_2608_23167_amd import api
+    from paper_2608_23167_amd.model import DeviceKVCache, DeviceModel
+    dims = dict(d_model=512, n_heads=4, n_kv_heads=4, ffn_dim=512) if base is LLADA_8B else {}
+    shape = dataclasses.replace(base, name="head", n_layers=0, vocab=vocab, mask_id=mask_id, **dims)
+    w = make_weights(shape, seed=5, device="cuda", norm_jitter=0.1, logit_scale=20.0)
+    n = vocab // 3
+    w.lm_head[n:2 * n] = w.lm_head[:n].clone()          # every one of these logits twice
+    w.lm_head[2 * n:2 * n + 9] = 0                       # and nine zeros
+    x = seeded_normal((1, rows, shape.d_model), 6, "head.x", device="cuda")
+    x[0, 0] = 0                                          # a row of equal logits
+    m = DeviceModel(shape, w)
+    cache = DeviceKVCache(dataclasses.replace(shape, n_layers=1), 1, rows)
+    out = (torch.zeros(rows, dtype=torch.int32, device="cuda"), torch.zeros(rows, device="cuda"),
+           torch.zeros(rows * k, dtype=torch.int32, device="cuda"), torch.zeros(rows * k, device="cuda"))
+    logits = torch.zeros(rows * vocab, device="cuda")
+    ws = torch.zeros(api.ssm_workspace_size(m, 1, rows), dtype=torch.uint8, device="cuda")
+    pos = torch.arange(rows, dtype=torch.int32, device="cuda")
+    api.ssm_denoise_step(m, cache, L.SSM_CACHE_OFF, 0, pos, rows, x, 0, k, *out, ws, logits=logits)
+    torch.cuda.synchronize()
+    quiet = tuple(torch.zeros_like(t) for t in out)      # without the logits stored
+    api.ssm_denoise_step(m, cache, L.SSM_CACHE_OFF, 0, pos, rows, x, 0, k, *quiet, ws)
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(out, quiet))
+    return (logits.view(rows, vocab).double().cpu(), out[0].cpu(), out[1].cpu(),
+            out[2].view(rows, k).cpu(), out[3].view(rows, k).cpu())
+
+
+@pytest.mark.parametrize("base,rows,vocab,k,mask_id", [
+    (LLADA_8B, 1, 128, 8, 127), (LLADA_8B, 63, 384, 5, 0), (LLADA_8B, 128, 1024, 8, 1000),
+    (LLADA_8B, 129, 1024, 8, 64), (LLADA_8B, 129, 640, 1, 639), (LLADA_8B, 257, 2048, 5, 2047),
+    (LLADA_8B, 300, 20480, 8, 700), (LLADA_8B, 120, 40960, 8, 40959),
+    (TINY, 33, 32, 8, 31), (TINY, 100, 4096, 5, 77)])
+def test_statistics_follow_the_logits(base, rows, vocab, k, mask_id):
+    """Ids are exact.  The sum of up to 4e4 float32 exponentials, in parts, is
+    off by a few hundred roundings at most: 5e-5."""
+    logits, argmax, conf, ids, w = _head(base, rows, vocab, k, mask_id)
+    z = logits.clone()
+    z[:, mask_id] = -float("inf")
+    order = torch.sort(z, dim=1, descending=True, stable=True)
+    assert torch.equal(ids.long(), order.indices[:, :k])
+    assert torch.equal(argmax.long(), order.indices[:, 0])
+    ref = torch.exp(order.values[:, 0] - torch.logsumexp(z, 1))
+    assert float((conf.double() / ref - 1).abs().max()) < 5e-5
+    ref_w = torch.softmax(order.values[:, :k], 1)
+    assert float((w.double() - ref_w).abs().max()) < 5e-5
