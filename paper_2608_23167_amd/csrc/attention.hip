@@ -568,49 +568,72 @@ __global__ void __launch_bounds__(512, 1) attn_dec_kernel(
   store_out4(O, s * Mq + q, h * DH + 16 * wave + 4 * g, v);
 }
 
-// float32 path: one thread per query row, keys read through the cache.
+// float32 path: a wave per query row, 4 rows a workgroup.  Per chunk of 64 keys
+// a lane scores one key (the query row comes from LDS, the same for all
+// lanes), the wave takes maximum and sum, and the probabilities go through LDS
+// to lanes that each own head dimensions: lane l dimensions DPL l .. of every
+// key (DH = 64, 128), or dimension l % 32 of the even or the odd keys (DH = 32).
+// A thread per row, as before, walks the keys alone: 108 rows and keys of 4
+// heads took 92 us.
 template <int DH>
-__global__ void __launch_bounds__(64) attn_f32_kernel(
+__global__ void __launch_bounds__(256) attn_f32_kernel(
     const float* __restrict__ Q, const float* __restrict__ Kc, const float* __restrict__ Vc,
     int H, int Hkv, int Mq, int Nk, int cap, int keys_per_split, float scale_log2,
     ActOut O, float* __restrict__ Opart, float* __restrict__ ML, Pads pads) {
+  constexpr int DPL = DH == 128 ? 2 : 1, KPI = DH == 32 ? 2 : 1;   // dims per lane, keys per step
+  __shared__ float q_all[4 * DH], p_all[4 * 64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int bh = blockIdx.y, s = bh / H, h = bh % H, kvh = h / (H / Hkv);
   const int split = blockIdx.z;
   const int kb = pads.of(s) + split * keys_per_split, ke = min(Nk, kb + keys_per_split);
-  const int q = blockIdx.x * 64 + threadIdx.x;
-  if (q >= Mq) return;
-  const float* qp = Q + ((size_t)bh * Mq + q) * DH;
-  float qv[DH], ov[DH];
-#pragma unroll
-  for (int c = 0; c < DH; ++c) { qv[c] = qp[c]; ov[c] = 0.f; }
+  const int q = blockIdx.x * 4 + wave;
+  if (q >= Mq) return;                           // no barrier below: a wave is on its own
+  float* const qs = q_all + wave * DH;
+  float* const ps = p_all + wave * 64;
+  for (int c = lane; c < DH; c += 64) qs[c] = Q[((size_t)bh * Mq + q) * DH + c];
+  __builtin_amdgcn_wave_barrier();               // LDS accesses of one wave stay in order
   const float* Kh = Kc + (size_t)(s * Hkv + kvh) * cap * DH;
   const float* Vh = Vc + (size_t)(s * Hkv + kvh) * cap * DH;
-  float m_run = -INFINITY, l_run = 0.f;
-  for (int j = kb; j < ke; ++j) {
-    const float* kp = Kh + (size_t)j * DH;
+  const int sub = KPI == 2 ? lane >> 5 : 0, dim = KPI == 2 ? lane & 31 : lane * DPL;
+  float o[DPL], m_run = -INFINITY, l_run = 0.f;
+#pragma unroll
+  for (int d = 0; d < DPL; ++d) o[d] = 0.f;
+  for (int k0 = kb; k0 < ke; k0 += 64) {
+    const bool in = k0 + lane < ke;
+    const float* kp = Kh + (size_t)min(k0 + lane, ke - 1) * DH;
     float dot = 0.f;
 #pragma unroll
-    for (int c = 0; c < DH; ++c) dot = fmaf(qv[c], kp[c], dot);
-    const float sv = dot * scale_log2;
-    const float m_new = fmaxf(m_run, sv);
-    const float alpha = exp2f(m_run - m_new), p = exp2f(sv - m_new);
-    l_run = l_run * alpha + p;
-    const float* vp = Vh + (size_t)j * DH;
-#pragma unroll
-    for (int c = 0; c < DH; ++c) ov[c] = ov[c] * alpha + p * vp[c];
+    for (int c = 0; c < DH; ++c) dot = fmaf(qs[c], kp[c], dot);
+    const float sv = in ? dot * scale_log2 : -INFINITY;
+    const float m_new = fmaxf(m_run, wave_max(sv));
+    const float alpha = exp2f(m_run - m_new), p = in ? exp2f(sv - m_new) : 0.f;
+    l_run = l_run * alpha + wave_sum(p);
     m_run = m_new;
+    __builtin_amdgcn_wave_barrier();
+    ps[lane] = p;
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int d = 0; d < DPL; ++d) o[d] *= alpha;
+#pragma unroll 16
+    for (int i = 0; i < 64; i += KPI) {          // past the range: p = 0, the last key again
+      const float pi = ps[i + sub];
+      const float* vp = Vh + (size_t)min(k0 + i + sub, ke - 1) * DH + dim;
+#pragma unroll
+      for (int d = 0; d < DPL; ++d) o[d] = fmaf(pi, vp[d], o[d]);
+    }
   }
+  if (KPI == 2) o[0] += __shfl_xor(o[0], 32, 64);
+  if (sub) return;
   if (Opart == nullptr) {
-    float* out = (float*)O.hi + ((size_t)s * Mq + q) * O.ld + h * DH;
+    float* out = (float*)O.hi + ((size_t)s * Mq + q) * O.ld + h * DH + dim;
     const float inv = 1.0f / l_run;
 #pragma unroll
-    for (int c = 0; c < DH; ++c) out[c] = ov[c] * inv;
+    for (int d = 0; d < DPL; ++d) out[d] = o[d] * inv;
   } else {
     const size_t row = ((size_t)split * gridDim.y + bh) * Mq + q;
 #pragma unroll
-    for (int c = 0; c < DH; ++c) Opart[row * DH + c] = ov[c];
-    ML[row * 2] = m_run;
-    ML[row * 2 + 1] = l_run;
+    for (int d = 0; d < DPL; ++d) Opart[row * DH + dim + d] = o[d];
+    if (lane == 0) { ML[row * 2] = m_run; ML[row * 2 + 1] = l_run; }
   }
 }
 
@@ -695,8 +718,7 @@ hipError_t attention(int dtype, const void* q, const void* kc, const void* vc, i
   // bfloat16 / float16: 32 query rows per wave (128 per workgroup), which
   // halves the LDS reads per MFMA, once 64-row tiles alone would give two
   // workgroups per CU; below that 16 per wave, twice the workgroups for a
-  // launch that is bound by latency rather than by MFMA or HBM.  float32: 64
-  // rows per block.
+  // launch that is bound by latency rather than by MFMA or HBM.
   const bool mfma = dtype == ATTN_BF16 || dtype == ATTN_F16;
   const int QB = attention_qb(dtype, BH, Mq);
   const int qtiles = ceil_div(Mq, 64 * QB);
@@ -734,19 +756,19 @@ hipError_t attention(int dtype, const void* q, const void* kc, const void* vc, i
       else go(attn_bf16_kernel<1, bf16_t, 1>, 256, qh, kh, vh);
     }
   } else {
-    const dim3 grid(qtiles, BH, S);
+    const dim3 grid(ceil_div(Mq, 4), BH, S);
     const float* qf = (const float*)q;
     const float* kf = (const float*)kc;
     const float* vf = (const float*)vc;
     const ActOut& of = out;
     if (dh == 32)
-      launch(attn_f32_kernel<32>, grid, dim3(64), 0, st, qf, kf, vf, H, Hkv, Mq, Nk,
+      launch(attn_f32_kernel<32>, grid, dim3(256), 0, st, qf, kf, vf, H, Hkv, Mq, Nk,
                          cap, kps, scale_log2, of, opart, ws.ml, pads);
     else if (dh == 64)
-      launch(attn_f32_kernel<64>, grid, dim3(64), 0, st, qf, kf, vf, H, Hkv, Mq, Nk,
+      launch(attn_f32_kernel<64>, grid, dim3(256), 0, st, qf, kf, vf, H, Hkv, Mq, Nk,
                          cap, kps, scale_log2, of, opart, ws.ml, pads);
     else
-      launch(attn_f32_kernel<128>, grid, dim3(64), 0, st, qf, kf, vf, H, Hkv, Mq, Nk,
+      launch(attn_f32_kernel<128>, grid, dim3(256), 0, st, qf, kf, vf, H, Hkv, Mq, Nk,
                          cap, kps, scale_log2, of, opart, ws.ml, pads);
   }
   if (S > 1) {

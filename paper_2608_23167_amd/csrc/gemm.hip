@@ -888,36 +888,60 @@ __global__ void __launch_bounds__(512, 2) gemm_pp_kernel(Pol pol, const bf16_t* 
 }
 
 // ---------------------------------------------------------------------------
-// float32 kernel (fp32 mode): 32x32 tiles, BK = 32, 256 threads, 4 outputs each
+// float32 kernel (fp32 mode): 32 x 32 tiles, 256 threads, 4 outputs each
 // ---------------------------------------------------------------------------
+// Both operands of up to 128 K columns are in flight at once and go through
+// LDS transposed (k rows of 36 floats: 16-byte aligned, so a thread reads its
+// 4 columns at once).  The small model's launches are bound by the trips to
+// memory: with 32 columns a trip, the 108-row projections took 5 to 11 us.
 template <class Pol>
 __global__ void __launch_bounds__(256) gemm_f32_kernel(Pol pol, const float* __restrict__ A, int lda,
                                                        int M, int k_per_split,
                                                        float* __restrict__ part, int ldp) {
-  constexpr int BM = 32, BN = 32, BK = 32, CS = BN + 1;
-  __shared__ float As[BK][BM + 1];
-  __shared__ float Bs[BK][BN + 1];
+  constexpr int BM = 32, BN = 32, BK = 128, LD = 36, CS = BN + 1, NQ = BK / 32;
+  __shared__ __attribute__((aligned(16))) float As[BK][LD];
+  __shared__ __attribute__((aligned(16))) float Bs[BK][LD];
   __shared__ float Cs[BM * CS];
   const int tid = threadIdx.x;
   const int t = blockIdx.x, m0 = blockIdx.y * BM, split = blockIdx.z;
-  const int kbeg = split * k_per_split;
+  const int kbeg = split * k_per_split, kend = kbeg + k_per_split;
   const float *blo, *bhi;
   pol.b_ptrs(t, BN, blo, bhi);
+  // copies: row tid / 8 of each operand, columns 4 (tid % 8) + 32 q (k_per_split
+  // is a multiple of 32, so a 32-column group is in or out as a whole)
+  const int cr = tid >> 3, cc = (tid & 7) * 4;
+  const float* ap = A + (size_t)min(m0 + cr, M - 1) * lda + cc;
+  const float* bp = (cr < BN / 2 ? blo + (size_t)cr * pol.ldb : bhi + (size_t)(cr - BN / 2) * pol.ldb) + cc;
   const int tr = tid / 8, tc = (tid % 8) * 4;   // output row, first of 4 columns
   float acc[4] = {0.f, 0.f, 0.f, 0.f};
-  for (int k0 = kbeg; k0 < kbeg + k_per_split; k0 += BK) {
-    for (int idx = tid; idx < BM * BK; idx += 256) {
-      const int r = idx / BK, kk = idx % BK;
-      As[kk][r] = A[(size_t)min(m0 + r, M - 1) * lda + k0 + kk];
-      const float* rp = r < BN / 2 ? blo + (size_t)r * pol.ldb : bhi + (size_t)(r - BN / 2) * pol.ldb;
-      Bs[kk][r] = rp[k0 + kk];
-    }
-    __syncthreads();
-#pragma unroll 8
-    for (int kk = 0; kk < BK; ++kk) {
-      const float a = As[kk][tr];
+  for (int k0 = kbeg; k0 < kend; k0 += BK) {
+    f32x4_t av[NQ], bv[NQ];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) acc[j] = fmaf(a, Bs[kk][tc + j], acc[j]);
+    for (int q = 0; q < NQ; ++q)
+      if (k0 + 32 * q < kend) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {            // rows of any 4-byte alignment
+          av[q][e] = ap[k0 + 32 * q + e];
+          bv[q][e] = bp[k0 + 32 * q + e];
+        }
+      }
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+      if (k0 + 32 * q < kend) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          As[32 * q + cc + e][cr] = av[q][e];
+          Bs[32 * q + cc + e][cr] = bv[q][e];
+        }
+      }
+    __syncthreads();
+    const int kn = min(BK, kend - k0);
+#pragma unroll 16
+    for (int kk = 0; kk < kn; ++kk) {
+      const float a = As[kk][tr];
+      const f32x4_t b = *(const f32x4_t*)&Bs[kk][tc];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[j] = fmaf(a, b[j], acc[j]);
     }
     __syncthreads();
   }
@@ -1221,15 +1245,27 @@ static hipError_t run_bf16(const char* kind, Pol pol, const ActIn& a, int M, int
   return launch_plan(pol, a, M, K, N, c, ws, st);
 }
 
+// Eight gains, 16-byte aligned.
+__device__ __forceinline__ void load_gain8(const bf16_t* g, float (&v)[8]) {
+  const u32x4_t w = *(const u32x4_t*)g;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) v[e] = __uint_as_float(e & 1 ? (w[e >> 1] & 0xffff0000u) : (w[e >> 1] << 16));
+}
+__device__ __forceinline__ void load_gain8(const float* g, float (&v)[8]) {
+  const float4 a = ((const float4*)g)[0], b = ((const float4*)g)[1];
+  v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
+  v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
+}
+
 // Completion of a split-K residual projection fused with the RMSNorm that
 // follows it: resid[m] += sum over splits of part[s][m] (split order, as the
 // split-K reduction does), then y[m] = resid[m] / rms(resid[m]) * g as the next
 // projection's operand.  One workgroup of 512 threads per row; thread t holds
 // the 8-column chunks t + 512 q of the row (q < NC).
-template <int SC, int NC>
+template <typename T, int SC, int NC>
 __global__ void __launch_bounds__(512) resid_norm_kernel(const float* __restrict__ part, int S,
                                                          int M, int N, float* __restrict__ resid,
-                                                         const bf16_t* __restrict__ g, float eps,
+                                                         const T* __restrict__ g, float eps,
                                                          ActOut y) {
   __shared__ float red[8];
   const int m = xcd_row(blockIdx.x, gridDim.x), tid = threadIdx.x, nc8 = N >> 3;
@@ -1261,41 +1297,58 @@ __global__ void __launch_bounds__(512) resid_norm_kernel(const float* __restrict
   for (int q = 0; q < NC; ++q) {
     const int c8 = tid + 512 * q;
     if (c8 >= nc8) continue;
-    const u32x4_t gw = *(const u32x4_t*)(g + c8 * 8);
-    float o[8];
+    float ge[8], o[8];
+    load_gain8(g + c8 * 8, ge);
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const uint32_t w = gw[e >> 1];
-      const float ge = __uint_as_float(e & 1 ? (w & 0xffff0000u) : (w << 16));
-      o[e] = v[q][e] * inv * ge;
-    }
-    y.store8<bf16_t>(m, c8 * 8, o);
+    for (int e = 0; e < 8; ++e) o[e] = v[q][e] * inv * ge[e];
+    y.store8<T>(m, c8 * 8, o);
   }
 }
 
-template <int SC>
-static void launch_resid_norm(int nc, int S, int M, int N, const float* part, float* resid,
-                              const NormTo* nrm, hipStream_t st) {
-  const bf16_t* g = (const bf16_t*)nrm->g;
-  if (nc == 1)
-    launch(resid_norm_kernel<SC, 1>, dim3(M), dim3(512), 0, st, part, S, M, N, resid, g, nrm->eps, nrm->y);
+template <typename T, int SC>
+static void launch_resid_norm_s(int S, int M, int N, const float* part, float* resid,
+                                const NormTo* nrm, hipStream_t st) {
+  const T* g = (const T*)nrm->g;
+  if (N <= 4096)
+    launch(resid_norm_kernel<T, SC, 1>, dim3(M), dim3(512), 0, st, part, S, M, N, resid, g, nrm->eps, nrm->y);
   else
-    launch(resid_norm_kernel<SC, 2>, dim3(M), dim3(512), 0, st, part, S, M, N, resid, g, nrm->eps, nrm->y);
+    launch(resid_norm_kernel<T, SC, 2>, dim3(M), dim3(512), 0, st, part, S, M, N, resid, g, nrm->eps, nrm->y);
+}
+template <typename T>
+static void launch_resid_norm(int S, int M, int N, const float* part, float* resid,
+                              const NormTo* nrm, hipStream_t st) {
+  if (S == 8) launch_resid_norm_s<T, 8>(S, M, N, part, resid, nrm, st);
+  else if (S == 4) launch_resid_norm_s<T, 4>(S, M, N, part, resid, nrm, st);
+  else if (S == 3) launch_resid_norm_s<T, 3>(S, M, N, part, resid, nrm, st);
+  else if (S == 2) launch_resid_norm_s<T, 2>(S, M, N, part, resid, nrm, st);
+  else launch_resid_norm_s<T, 0>(S, M, N, part, resid, nrm, st);
+}
+// Whether resid_norm_kernel can take the split-K sums of this projection.
+static bool resid_norm_ok(int S, int N, const NormTo* nrm) {
+  return nrm && S > 1 && N % 8 == 0 && N <= 8192 && ((uintptr_t)nrm->g & 15) == 0;
+}
+
+// float32 projections: split-K while CUs are idle and every split keeps 128
+// columns, one trip to memory (a shorter one costs the same and the sum a launch).
+static int f32_split(int M, int K, int N, size_t ws_floats) {
+  const int tiles = (N / 32) * ceil_div(M, 32);
+  int S = 1;
+  while (S < 8 && tiles * S < 256 && K % (32 * S * 2) == 0 && K / (S * 2) >= 128 &&
+         (S * 2) * M <= SPLIT_ROWS_MAX && (size_t)(S * 2) * M * N <= ws_floats)
+    S *= 2;
+  return S;
 }
 
 template <class Pol>
 static hipError_t run_f32(const Pol& pol, const ActIn& a, int M, int K, int N, SplitWs ws,
-                          hipStream_t st) {
+                          hipStream_t st, bool reduce = true) {
   constexpr int BN = 32;
   const int ntiles = N / BN, mt = ceil_div(M, 32);
-  int S = 1;
-  while (S < 8 && ntiles * mt * S < 256 && K % (32 * S * 2) == 0 && (S * 2) * M <= SPLIT_ROWS_MAX &&
-         (size_t)(S * 2) * M * N <= ws.floats)
-    S *= 2;
+  const int S = f32_split(M, K, N, ws.floats);
   dim3 grid(ntiles, mt, S);
   launch((gemm_f32_kernel<Pol>), grid, dim3(256), 0, st, pol, (const float*)a.hi,
                      a.ld, M, K / S, S > 1 ? ws.part : nullptr, N);
-  if (S > 1) launch_reduce<BN>(pol, ws.part, N, M, S, ntiles, st);
+  if (S > 1 && reduce) launch_reduce<BN>(pol, ws.part, N, M, S, ntiles, st);
   return hipGetLastError();
 }
 
@@ -1365,27 +1418,24 @@ hipError_t gemm_qkv(int dtype, const ActIn& a, int M, int d, const void* wq, con
 hipError_t gemm_resid(int dtype, const char* kind, const ActIn& a, int M, int K, const void* w,
                       int N, float* resid, SplitWs ws, hipStream_t st, const NormTo* nrm) {
   hipError_t e;
+  bool fuse;
   if (dtype == 0) {
     PolResid<float> p{(const float*)w, K, N, resid};
-    e = run_f32(p, a, M, K, N, ws, st);
+    const int S = f32_split(M, K, N, ws.floats);
+    fuse = resid_norm_ok(S, N, nrm);
+    e = run_f32(p, a, M, K, N, ws, st, !fuse);
+    if (e == hipSuccess && fuse) launch_resid_norm<float>(S, M, N, ws.part, resid, nrm, st);
   } else {
     PolResid<bf16_t> p{(const bf16_t*)w, K, N, resid};
     const GemmCfg c = plan_bf16(kind, p, M, K, N, a.lo != nullptr,
                                 default_cfg(kind, M, a.lo != nullptr), ws,
                                 any_bn<PolResid<bf16_t>>);
-    const int nc = ceil_div(N / 8, 512);
-    const bool fuse = nrm && c.s > 1 && N % 8 == 0 && nc <= 2 && ((uintptr_t)nrm->g & 15) == 0;
+    fuse = resid_norm_ok(c.s, N, nrm);
     e = launch_plan(p, a, M, K, N, c, ws, st, !fuse);
-    if (e != hipSuccess || !fuse) goto separate;
-    if (c.s == 8) launch_resid_norm<8>(nc, c.s, M, N, ws.part, resid, nrm, st);
-    else if (c.s == 4) launch_resid_norm<4>(nc, c.s, M, N, ws.part, resid, nrm, st);
-    else if (c.s == 3) launch_resid_norm<3>(nc, c.s, M, N, ws.part, resid, nrm, st);
-    else if (c.s == 2) launch_resid_norm<2>(nc, c.s, M, N, ws.part, resid, nrm, st);
-    else launch_resid_norm<0>(nc, c.s, M, N, ws.part, resid, nrm, st);
-    return hipGetLastError();
+    if (e == hipSuccess && fuse) launch_resid_norm<bf16_t>(c.s, M, N, ws.part, resid, nrm, st);
   }
-separate:
   if (e != hipSuccess || !nrm) return e;
+  if (fuse) return hipGetLastError();
   return launch_norm(dtype, resid, N, nrm->g, nrm->eps, nrm->y, M, M, 0, 0, st);
 }
 

@@ -47,7 +47,7 @@ __device__ __forceinline__ void stat_combine(float& m, float& s, float om, float
   m = M;
 }
 
-struct RowStatShared {
+struct __attribute__((aligned(16))) RowStatShared {
   long long key[256];
   float m[4], s[4], cv[64], bv[STAT_K], tv;
   int ci[64], bi[STAT_K], ti;
@@ -82,8 +82,12 @@ __device__ __forceinline__ void row_stats_end(RowStatShared& sh, float m, float 
   if (lane == 0) { sh.m[wave] = m; sh.s[wave] = s; }
   __syncthreads();
   int rank = 0;
+  const longlong2* keys = (const longlong2*)sh.key;
 #pragma unroll 16
-  for (int u = 0; u < 256; ++u) rank += sh.key[u] > key;
+  for (int u = 0; u < 128; ++u) {
+    const longlong2 k2 = keys[u];
+    rank += (k2.x > key) + (k2.y > key);
+  }
   const bool lists = rank < STAT_K && i != STAT_NONE;   // ids are unique
   if (lists && rank == STAT_K - 1) { sh.tv = v; sh.ti = i; }
   __syncthreads();
