@@ -1062,7 +1062,15 @@ static constexpr int PP_SLOTS = 256;
 static constexpr float PP_FIXED_US = 8.0f;
 // float32 partials of split-K are written once and read once
 static constexpr float PP_PARTIAL_BYTES_PER_US = 5.0e6f;
-static constexpr int PP_MAX_SPLIT = 4;
+static constexpr float WEIGHT_BYTES_PER_US = 5.5e6f;   // weights from HBM
+static constexpr float SPLIT_SUM_US = 4.0f;            // the launch that sums partials
+// (more than 4 splits pay only where their partials are small)
+static int pp_max_split(int M) { return M <= 256 ? 8 : 4; }
+// gemm_bf16_kernel: its K-step grows with the tile's columns and rows (us, from
+// 60-240 rows of 4096-18944 columns), the fixed part as above.
+static float bf16_step_us(int bn, int bm, bool pair) {
+  return 0.27f + 0.0029f * bn * (bm / 128.0f) * (pair ? 2 : 1);
+}
 
 // Per-projection launch choice: tile width BN (64, 96 or 128), split-K S
 // (0 = automatic) and the depth PW (4 or 8 K-steps) of the staging waves'
@@ -1108,13 +1116,20 @@ static int auto_split(int tiles, int M, int K, size_t ws_floats, int N) {
   return S;
 }
 
-// Time of gemm_pp_kernel with tile number `tile` (1 + its index) and split S, in us.
+// Time of the sum of S split-K partials (0 for one), in us.
+static float split_sum_us(int M, int N, int S) {
+  return S > 1 ? 8.0f * S * M * N / PP_PARTIAL_BYTES_PER_US + SPLIT_SUM_US : 0.f;
+}
+
+// Time of gemm_pp_kernel with tile number `tile` (1 + its index) and split S, in
+// us; never below the time the weights take from HBM.
 static float pp_cost(int tile, int M, int K, int N, bool pair, int S = 1) {
   const PpTile& p = PP_TILES[tile - 1];
   const long wgs = (long)(N / p.bn) * ceil_div(M, p.bm) * S;
   const float steps = (float)ceil_div(K / 64, S) * (pair ? 2 : 1);
-  return (float)((wgs + PP_SLOTS - 1) / PP_SLOTS) * (steps * p.us + PP_FIXED_US) +
-         (S > 1 ? 8.0f * S * M * N / PP_PARTIAL_BYTES_PER_US : 0.f);
+  const float mfma = (float)((wgs + PP_SLOTS - 1) / PP_SLOTS) * (steps * p.us + PP_FIXED_US);
+  const float hbm = 2.0f * N * K / WEIGHT_BYTES_PER_US + PP_FIXED_US;
+  return (mfma > hbm ? mfma : hbm) + split_sum_us(M, N, S);
 }
 
 // The tile (1 + its index) and split of gemm_pp_kernel that cost least by the
@@ -1128,7 +1143,7 @@ static int pp_plan(const Pol& pol, int M, int K, int N, bool pair, size_t ws_flo
   for (int i = 0; i < N_PP_TILES; ++i) {
     const PpTile& p = PP_TILES[i];
     if ((want > 0 && want != i + 1) || N % p.bn != 0 || !bn_ok(pol, p.bn)) continue;
-    for (int S = 1; S <= PP_MAX_SPLIT; ++S) {
+    for (int S = 1; S <= pp_max_split(M); ++S) {
       if ((s > 0 && S != s) || S > K / 64 || (S > 1 && (size_t)S * M * N > ws_floats)) continue;
       const float us = pp_cost(i + 1, M, K, N, pair, S);
       if (!best || us < best_us) {
@@ -1188,7 +1203,9 @@ static hipError_t launch_bf16_bm(const Pol& pol, const ActIn& a, int M, int K, i
 template <class Pol>
 static GemmCfg plan_bf16(const char* kind, const Pol& pol, int M, int K, int N, bool pair, GemmCfg c,
                          const SplitWs& ws, int (*bn_ok)(const Pol&, int)) {
+  const GemmCfg given = c;
   c = cfg_override(kind, c);
+  const bool overridden = c.bn != given.bn || c.s != given.s || c.pp != given.pp || c.bm != given.bm || c.pw != given.pw;
   if (c.pp != 0 && !has_tile<Pol>::value && K % 64 == 0) {
     c.pp = pp_plan(pol, M, K, N, pair, ws.floats, bn_ok, c.pp, c.s);
     if (c.pp) return c;
@@ -1200,6 +1217,24 @@ static GemmCfg plan_bf16(const char* kind, const Pol& pol, int M, int K, int N, 
   const int tiles = (N / c.bn) * ceil_div(M, c.bm);
   int S = c.s > 0 ? c.s : auto_split(tiles, M, K, ws.floats, N);
   while (S > 1 && (K % (256 * S) != 0 || (size_t)S * M * N > ws.floats)) S /= 2;
+  // widths that leave this kernel with few workgroups or a nearly empty last
+  // round: gemm_pp_kernel, whose splits need not divide K, if it should take
+  // less than 0.7 of the time (grouped-query shape at 120 rows: gate/up, 296
+  // tiles, 84 -> 71 us; down, 28 tiles in 2 splits, 95 -> 48 us).  At 0.8 the
+  // estimate is not safe: several workgroups of this kernel may share a CU
+  // (gate/up with the pair at 330 rows, 135 us, would move to 148)
+  if (!has_tile<Pol>::value && K % 64 == 0 && !overridden) {
+    const float us = (float)ceil_div(tiles * S, 256) *
+                         (K / 64 / S * bf16_step_us(c.bn, c.bm, pair) + PP_FIXED_US) +
+                     split_sum_us(M, N, S);
+    int ps = 0;
+    const int tile = pp_plan(pol, M, K, N, pair, ws.floats, bn_ok, -1, ps);
+    if (tile && pp_cost(tile, M, K, N, pair, ps) < 0.7f * us) {
+      c.pp = tile;
+      c.s = ps;
+      return c;
+    }
+  }
   c.s = S;
   return c;
 }
@@ -1378,7 +1413,7 @@ static hipError_t run_f32(const Pol& pol, const ActIn& a, int M, int K, int N, S
 //    8-way split.
 static GemmCfg default_cfg(const char* kind, int M, bool paired) {
   if (!strcmp(kind, "lm")) return GemmCfg{128, 1, 4, M > 128 ? -1 : 0};
-  if (M > (paired ? 384 : 256)) return GemmCfg{128, 0, 4, -1};
+  if (M > (paired ? (!strcmp(kind, "qkv") ? 352 : 384) : 256)) return GemmCfg{128, 0, 4, -1};
   if (!strcmp(kind, "qkv")) return GemmCfg{96, 0, 4, 0};
   if (!strcmp(kind, "gate_up")) {
     GemmCfg c{96, 1, 4, 0};
@@ -1518,10 +1553,15 @@ hipError_t lm_head_stats(const ActIn& a, int M, int K, const void* w, int N, int
   const GemmCfg c = cfg_override("lm", default_cfg("lm", M, a.lo != nullptr));
   const SplitWs none{nullptr, 0};
   hipError_t e;
-  if (c.pp && N % 256 == 0) {
-    // one or two groups of 128 rows per tile, whichever takes less time
-    const bool pair = a.lo != nullptr;
-    e = pp_cost(1, M, K, N, pair) < pp_cost(4, M, K, N, pair)
+  // one or two groups of 128 rows per tile, whichever takes less time; a small
+  // vocabulary has too few 256-column tiles (2048 ids, 240 rows: 50 us on
+  // 128-column tiles, 68 on these)
+  const bool pair = a.lo != nullptr;
+  const float us1 = pp_cost(1, M, K, N, pair), us4 = pp_cost(4, M, K, N, pair);
+  const float us = (float)ceil_div(N / 128 * ceil_div(M, 128), 256) *
+                   (K / 64 * bf16_step_us(128, 128, pair) + PP_FIXED_US);
+  if (c.pp && N % 256 == 0 && (us1 < us4 ? us1 : us4) < us) {
+    e = us1 < us4
             ? launch_pp<256, 256, 2, 4>(p, a, M, K, N, 1, none, st, false)
             : launch_pp<128, 256, 2, 4>(p, a, M, K, N, 1, none, st, false);
   } else {
