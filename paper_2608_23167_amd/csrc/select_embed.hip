@@ -104,6 +104,11 @@ __device__ __forceinline__ void load8f(const float* p, float (&v)[8]) {
   v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
 }
 
+__device__ __forceinline__ void store8f(float* p, const float (&v)[8]) {
+  ((float4*)p)[0] = make_float4(v[0], v[1], v[2], v[3]);
+  ((float4*)p)[1] = make_float4(v[4], v[5], v[6], v[7]);
+}
+
 template <typename T>
 __global__ void __launch_bounds__(256) embed8_kernel(
     const T* __restrict__ E, int d, int vocab, int mask_id, int seq_len,
@@ -113,15 +118,17 @@ __global__ void __launch_bounds__(256) embed8_kernel(
     float alpha, float* __restrict__ x, Pads pads) {
   const int r = blockIdx.x, s = blockIdx.y, d8 = d >> 3;
   float* out = x + ((size_t)s * n_rows + r) * d;
-  const int p = pos[r] - pads.of(s);
-  const bool pad = pos[r] >= 0 && p < 0;
+  // the row's position, region and token in one trip to memory
+  const int row_pos = pos[r], row_region = region[r], row_tok = tok_c[(size_t)s * tok_stride + r];
+  const int p = row_pos - pads.of(s);
+  const bool pad = row_pos >= 0 && p < 0;
   const bool pos_ok = p >= 0 && p < seq_len;
   const size_t sp = (size_t)s * seq_len + (pos_ok ? p : 0);
-  const bool soft = pos_ok && region[r] >= 2 && prev_step >= 0 && pred_step[sp] == prev_step;
+  const bool soft = pos_ok && row_region >= 2 && prev_step >= 0 && pred_step[sp] == prev_step;
   const float qnan = __builtin_nanf("");
   SSM_DCHECK(k >= 1 && k <= 8 && (pos_ok || pad));
   if (!soft) {
-    const int tok = pad ? mask_id : tok_c[(size_t)s * tok_stride + r];
+    const int tok = pad ? mask_id : row_tok;
     const bool ok = (pos_ok || pad) && tok >= 0 && tok < vocab;
     SSM_DCHECK(ok);
     const T* e = E + (size_t)(ok ? tok : 0) * d;
@@ -132,8 +139,7 @@ __global__ void __launch_bounds__(256) embed8_kernel(
 #pragma unroll
         for (int j = 0; j < 8; ++j) v[j] = qnan;
       }
-      ((float4*)(out + 8 * c))[0] = make_float4(v[0], v[1], v[2], v[3]);
-      ((float4*)(out + 8 * c))[1] = make_float4(v[4], v[5], v[6], v[7]);
+      store8f(out + 8 * c, v);
     }
     return;
   }
@@ -167,8 +173,7 @@ __global__ void __launch_bounds__(256) embed8_kernel(
     load8f(em + 8 * c, m);
 #pragma unroll
     for (int j = 0; j < 8; ++j) v[j] = ok ? (1.0f - alpha) * m[j] + alpha * acc[j] : qnan;   // Eq. 8
-    ((float4*)(out + 8 * c))[0] = make_float4(v[0], v[1], v[2], v[3]);
-    ((float4*)(out + 8 * c))[1] = make_float4(v[4], v[5], v[6], v[7]);
+    store8f(out + 8 * c, v);
   }
 }
 
@@ -180,14 +185,12 @@ hipError_t launch_embed(int dtype, const void* E, int d, int vocab, int mask_id,
   if (n_rows == 0) return hipSuccess;
   dim3 grid(n_rows, batch);
   const bool vec = d % 8 == 0 && ((uintptr_t)E & 15) == 0 && ((uintptr_t)x & 15) == 0;
-  if (vec && dtype == 0)
-    launch(embed8_kernel<float>, grid, dim3(256), 0, st, (const float*)E, d, vocab, mask_id,
-           seq_len, tok_c, tok_stride, pos, region, n_rows, pred_ids, pred_w, pred_step,
-           prev_step, k, alpha, x, pads);
-  else if (vec)
-    launch(embed8_kernel<bf16_t>, grid, dim3(256), 0, st, (const bf16_t*)E, d, vocab, mask_id,
-           seq_len, tok_c, tok_stride, pos, region, n_rows, pred_ids, pred_w, pred_step,
-           prev_step, k, alpha, x, pads);
+  auto go = [&](auto kernel, auto* e) {
+    launch(kernel, grid, dim3(256), 0, st, e, d, vocab, mask_id, seq_len, tok_c, tok_stride, pos,
+           region, n_rows, pred_ids, pred_w, pred_step, prev_step, k, alpha, x, pads);
+  };
+  if (vec && dtype == 0) go(embed8_kernel<float>, (const float*)E);
+  else if (vec) go(embed8_kernel<bf16_t>, (const bf16_t*)E);
   else if (dtype == 0)
     launch(embed_kernel<float>, grid, dim3(256), 0, st, (const float*)E, d, vocab,
                        mask_id, seq_len, tok_c, tok_stride, pos, region, n_rows, pred_ids, pred_w,

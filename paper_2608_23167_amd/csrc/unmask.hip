@@ -42,9 +42,15 @@ __global__ void __launch_bounds__(256) unmask_kernel(
     uint8_t chosen = 0;
     if (cand[i]) {
       ++my_c;
-      int rank = 0;  // candidates ranked ahead: higher score, then lower position
-      for (int j = 0; j < b; ++j)
-        rank += cand[j] && (score[j] > score[i] || (score[j] == score[i] && j < i));
+      // candidates ranked ahead: higher score, then lower position.  No branch,
+      // so that the LDS reads of the block run ahead of the comparisons
+      const float mine = score[i];
+      int rank = 0;
+#pragma unroll 8
+      for (int j = 0; j < b; ++j) {
+        const float other = score[j];
+        rank += (cand[j] != 0) & ((other > mine) | ((other == mine) & (j < i)));
+      }
       if (rank == 0) best = i;
       chosen = rule == 0 ? (rank < n_per_step) : (score[i] > threshold);
     }
@@ -72,10 +78,21 @@ __global__ void __launch_bounds__(256) unmask_kernel(
     SSM_DCHECK(p >= 0 && p < seq_len);
     if (p < 0 || p >= seq_len) continue;
     const size_t sp = (size_t)s * seq_len + p;
-    for (int i = 0; i < k; ++i) {
-      pred_ids[sp * k + i] = topk_ids[(ro + r) * k + i];
-      pred_w[sp * k + i] = topk_w[(ro + r) * k + i];
-    }
+    // k <= 8: all loads first, one trip to memory
+    int ids[8];
+    float w[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      if (i < k) {
+        ids[i] = topk_ids[(ro + r) * k + i];
+        w[i] = topk_w[(ro + r) * k + i];
+      }
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      if (i < k) {
+        pred_ids[sp * k + i] = ids[i];
+        pred_w[sp * k + i] = w[i];
+      }
     pred_step[sp] = step;
   }
 }
