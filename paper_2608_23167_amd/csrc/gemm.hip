@@ -17,9 +17,8 @@
 //     the weight fragments from LDS and issue the MFMAs.
 // Splitting the roles keeps the in-order retirement of vector loads from
 // coupling the long HBM latency of the weights to the MFMA issue.  One
-// barrier per K-step (64) hands the LDS buffers over.  The output tile is
-// staged through LDS so that the epilogue can combine any two columns of the
-// tile and store coalesced.
+// barrier per K-step (64) hands the LDS buffers over.  The epilogue runs from
+// registers (whole-tile statistics from LDS).
 //
 // Every output tile of BN columns reads its first BN/2 weight rows from one
 // base pointer and its last BN/2 from another.  That is how the fused
@@ -391,9 +390,7 @@ template <int BM, int BN, int CS, class Pol>
 __device__ __forceinline__ void tile_epilogue(const Pol& pol, const float* Cs, int m0, int M,
                                               int t, float* part, int split, int ldp) {
   const int tid = threadIdx.x;
-  if constexpr (has_tile<Pol>::value) {
-    pol.template tile<BM, BN, CS>(Cs, m0, M, t);
-  } else if (part) {
+  if (part) {
     // float32 partial tile, 8 columns per thread
     for (int idx = tid; idx < BM * (BN / 8); idx += blockDim.x) {
       const int r = idx / (BN / 8), c0 = (idx % (BN / 8)) * 8, gm = m0 + r;
@@ -500,9 +497,12 @@ __global__ void __launch_bounds__(512) gemm_bf16_kernel(Pol pol, const bf16_t* _
   static_assert(AHEAD < PW, "the prologue refills the first AHEAD register sets");
   constexpr int BUF_ELEMS = BN * LS;
   constexpr int SMEM_W = NBUF * BUF_ELEMS * 2;
+  // the epilogue runs from registers; policies that look at a whole tile get it in LDS
+  constexpr bool TILE = has_tile<Pol>::value;
   constexpr int CS = BN + 4;
-  constexpr int SMEM_C = BM * CS * 4;
+  constexpr int SMEM_C = TILE ? BM * CS * 4 : 0;
   constexpr int SMEM = SMEM_W > SMEM_C ? SMEM_W : SMEM_C;
+  static_assert(TILE || !Pol::PAIRED || FN % 2 == 0, "halves of whole fragments");
   __shared__ __attribute__((aligned(16))) char smem[SMEM];
   bf16_t* Ws = (bf16_t*)smem;                    // [NBUF][BN][LS]
 
@@ -564,7 +564,7 @@ __global__ void __launch_bounds__(512) gemm_bf16_kernel(Pol pol, const bf16_t* _
     _Pragma("unroll") for (int i = 0; i < FM; ++i)                                    \
     _Pragma("unroll") for (int j = 0; j < FN; ++j)                                    \
         acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(                          \
-            __builtin_bit_cast(bf16x8_t, RA[p][i][KK]), F[j], acc[i][j], 0, 0, 0);     \
+            F[j], __builtin_bit_cast(bf16x8_t, RA[p][i][KK]), acc[i][j], 0, 0, 0);     \
   } while (0)
     // step kt: wf0 holds (kt, first half); read (kt, second half) into wf1,
     // use wf0; read (kt + 1, first half) into wf0, use wf1; fetch the
@@ -594,14 +594,36 @@ __global__ void __launch_bounds__(512) gemm_bf16_kernel(Pol pol, const bf16_t* _
         CSTEP(kt, a0);
         CSTEP(kt + 1, a1);
       }
-      // accumulators -> LDS tile: acc[i][j][r] = C[RW wave + 16i + 4*(lane/16) + r][16j + lane%16]
+      // acc[i][j][r] = C[RW wave + 16 i + lane % 16][16 j + 4 (lane / 16) + r]: the
+      // weights are the MFMA's first operand, so a lane holds 4 consecutive
+      // columns of a row, and both columns of a pair (tiles' halves are whole
+      // fragments)
+      const int c4 = 4 * (lane >> 4);
+      if constexpr (TILE) {
 #pragma unroll
-      for (int i = 0; i < FM; ++i)
+        for (int i = 0; i < FM; ++i)
 #pragma unroll
-        for (int j = 0; j < FN; ++j)
+          for (int j = 0; j < FN; ++j)
+            *(f32x4_t*)&Cs[(RW * wave + i * 16 + (lane & 15)) * CS + j * 16 + c4] = acc[i][j];
+      } else {
 #pragma unroll
-          for (int r = 0; r < 4; ++r)
-            Cs[(RW * wave + i * 16 + (lane >> 4) * 4 + r) * CS + j * 16 + (lane & 15)] = acc[i][j][r];
+        for (int i = 0; i < FM; ++i) {
+          const int m = m0 + RW * wave + 16 * i + (lane & 15);
+          if (m >= M) continue;
+          if (part) {
+            float* p = part + ((size_t)split * M + m) * ldp + (size_t)t * BN + c4;
+#pragma unroll
+            for (int j = 0; j < FN; ++j) *(f32x4_t*)(p + 16 * j) = acc[i][j];
+          } else if constexpr (Pol::PAIRED) {
+#pragma unroll
+            for (int j = 0; j < FN / 2; ++j)
+              pol.store4(m, t, 16 * j + c4, BN, acc[i][j], acc[i][j + FN / 2]);
+          } else {
+#pragma unroll
+            for (int j = 0; j < FN; ++j) pol.store4_1(m, t * BN + 16 * j + c4, acc[i][j]);
+          }
+        }
+      }
     }
 #undef LOAD_A
 #undef READ_W
@@ -652,8 +674,10 @@ __global__ void __launch_bounds__(512) gemm_bf16_kernel(Pol pol, const bf16_t* _
 #undef LOAD_S
 #undef STORE_S
   }
-  __syncthreads();
-  tile_epilogue<BM, BN, CS>(pol, Cs, m0, M, t, part, split, ldp);
+  if constexpr (TILE) {
+    __syncthreads();
+    pol.template tile<BM, BN, CS>(Cs, m0, M, t);
+  }
 }
 
 // Waits until at most N vector-memory operations of this wave are in flight.
