@@ -100,3 +100,38 @@ def test_float32_layer_at_tile_edges(dims, rows):
     ek = _worst(keys, ref_k)
     print(f"rows {rows} d {shape.d_model}: error over bound {np.max(err / bound):.2f}, keys {ek:.2e}")
     assert np.all(err < bound) and ek < 1e-5
+
+
+@pytest.mark.parametrize("d", [128, 1024])
+def test_float32_sums_in_short_chains(d):
+    """Error of the float32 head's logits, whose operand is exact here (rows of
+    +1 and -1 have a mean square of one, eps vanishes beside it, and the gains
+    are float32): nothing but the sums of d products rounds.  A chain of n
+    fused multiply-adds of random terms is off by 0.31 sqrt(n) 2^-24 of the
+    result (rms: each step rounds a partial sum of growing size by up to half a
+    unit in the last place).  Sums of 32 products, added up, give
+    0.31 sqrt(32 + d / 32) 2^-24; the bound is 1.25 times that.  One chain of d
+    products would give 3.5 (d = 128), four chains of a quarter 4.7 (d = 1024)."""
+    import dataclasses
+    from paper_2608_23167_amd import _lib as L
+    from paper_2608_23167_amd import api
+    from paper_2608_23167_amd.model import DeviceKVCache, DeviceModel
+    rows, vocab = 108, 512
+    shape = dataclasses.replace(TINY, name="chains", n_layers=0, d_model=d, n_heads=d // 32,
+                                n_kv_heads=d // 32, vocab=vocab, mask_id=vocab - 1, rms_eps=1e-30)
+    w = make_weights(shape, seed=7, device="cuda", norm_jitter=0.1)
+    g = torch.Generator(device="cuda").manual_seed(8)
+    x = torch.randint(0, 2, (1, rows, d), generator=g, device="cuda").float() * 2 - 1
+    m = DeviceModel(shape, w)
+    cache = DeviceKVCache(dataclasses.replace(shape, n_layers=1), 1, rows)
+    out = (torch.zeros(rows, dtype=torch.int32, device="cuda"), torch.zeros(rows, device="cuda"),
+           torch.zeros(rows, dtype=torch.int32, device="cuda"), torch.zeros(rows, device="cuda"))
+    logits = torch.zeros(rows * vocab, device="cuda")
+    ws = torch.zeros(api.ssm_workspace_size(m, 1, rows), dtype=torch.uint8, device="cuda")
+    pos = torch.arange(rows, dtype=torch.int32, device="cuda")
+    api.ssm_denoise_step(m, cache, L.SSM_CACHE_OFF, 0, pos, rows, x, 0, 1, *out, ws, logits=logits)
+    torch.cuda.synchronize()
+    ref = (x[0].double() * w.final_norm.double()).cpu() @ w.lm_head.double().cpu().T
+    err = float((logits.view(rows, vocab).double().cpu() - ref).norm() / ref.norm()) * 2 ** 24
+    print(f"d {d}: rms error {err:.2f} x 2^-24")
+    assert err < 1.25 * 0.31 * (32 + d / 32) ** 0.5
