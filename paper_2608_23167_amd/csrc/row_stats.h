@@ -38,12 +38,11 @@ __device__ __forceinline__ float ordered_float(int o) {
   return __int_as_float(o ^ ((o >> 31) & 0x7fffffff));
 }
 
-// (max, sum of exp(x - max)) pairs: s == 0 is an empty one.
+// (max, sum of exp(x - max)) pairs: s == 0 adds nothing to a sum, but its
+// maximum counts.  Two pairs that meet at an infinite maximum give NaN.
 __device__ __forceinline__ void stat_combine(float& m, float& s, float om, float os) {
-  if (!(os > 0.f)) return;
-  if (!(s > 0.f)) { m = om; s = os; return; }
   const float M = fmaxf(m, om);
-  s = s * expf(m - M) + os * expf(om - M);
+  s = (s == 0.f ? 0.f : s * expf(m - M)) + (os == 0.f ? 0.f : os * expf(om - M));
   m = M;
 }
 
@@ -66,6 +65,7 @@ __device__ __forceinline__ void row_stats_end(RowStatShared& sh, float m, float 
                                               int row, int k, int32_t* argmax, float* conf,
                                               int32_t* topk_ids, float* topk_w, Fill fill) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (!(s > 0.f)) s = 0.f;    // empty, or NaN among its values
   // id STAT_NONE sorts last among -inf
   const long long key = ((long long)ordered_bits(v) << 32) | (unsigned)(STAT_NONE - i);
   sh.key[tid] = key;

@@ -61,3 +61,37 @@ def test_statistics_follow_the_logits(base, rows, vocab, k, mask_id):
     assert float((conf.double() / ref - 1).abs().max()) < 5e-5
     ref_w = torch.softmax(order.values[:, :k], 1)
     assert float((w.double() - ref_w).abs().max()) < 5e-5
+
+
+@pytest.mark.parametrize("base,vocab", [(TINY, 512), (LLADA_8B, 1024)])
+def test_infinite_logits(base, vocab):
+    """A row whose best logit is +inf has no finite confidence (exp(inf - inf));
+    logits of -inf count for nothing.  An infinite weight gives both: rows whose
+    operand is positive there get +inf, the others -inf."""
+    from paper_2608_23167_amd import _lib as L
+    from paper_2608_23167_amd import api
+    from paper_2608_23167_amd.model import DeviceKVCache, DeviceModel
+    rows, k, mask_id = 40, 5, vocab - 1
+    dims = dict(d_model=512, n_heads=4, n_kv_heads=4, ffn_dim=512) if base is LLADA_8B else {}
+    shape = dataclasses.replace(base, name="head", n_layers=0, vocab=vocab, mask_id=mask_id, **dims)
+    w = make_weights(shape, seed=5, device="cuda", norm_jitter=0.1, logit_scale=20.0)
+    w.lm_head[77, 3] = float("inf")
+    x = seeded_normal((1, rows, shape.d_model), 6, "head.inf", device="cuda")
+    m = DeviceModel(shape, w)
+    cache = DeviceKVCache(dataclasses.replace(shape, n_layers=1), 1, rows)
+    argmax, conf = torch.zeros(rows, dtype=torch.int32, device="cuda"), torch.zeros(rows, device="cuda")
+    ids, tw = torch.zeros(rows * k, dtype=torch.int32, device="cuda"), torch.zeros(rows * k, device="cuda")
+    logits = torch.zeros(rows * vocab, device="cuda")
+    ws = torch.zeros(api.ssm_workspace_size(m, 1, rows), dtype=torch.uint8, device="cuda")
+    pos = torch.arange(rows, dtype=torch.int32, device="cuda")
+    api.ssm_denoise_step(m, cache, L.SSM_CACHE_OFF, 0, pos, rows, x, 0, k, argmax, conf, ids, tw, ws,
+                         logits=logits)
+    torch.cuda.synchronize()
+    z = logits.view(rows, vocab).double().cpu()
+    z[:, mask_id] = -float("inf")
+    up = x[0, :, 3].cpu() > 0
+    assert 0 < int(up.sum()) < rows and torch.equal(z[:, 77] == float("inf"), up)
+    assert torch.equal(argmax.cpu().long(), z.argmax(1))
+    assert not torch.isfinite(conf.cpu()[up]).any()
+    ref = torch.softmax(z[~up], 1).amax(1)
+    assert float((conf.cpu()[~up].double() / ref - 1).abs().max()) < 5e-5
