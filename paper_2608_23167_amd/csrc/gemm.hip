@@ -89,6 +89,7 @@ struct PolQKV {
   const float2* rope;
   int rope_per_seq;    // 1: RoPE table [B, n_rows, d_h / 2] (padded batch), 0: [n_rows, d_h / 2]
 
+  uintptr_t weight_bits() const { return (uintptr_t)wq | (uintptr_t)wk | (uintptr_t)wv; }
   __device__ __forceinline__ const T* head_rows(int head) const {
     if (head < H) return wq + (size_t)head * dh * ldb;
     if (head < H + Hkv) return wk + (size_t)(head - H) * dh * ldb;
@@ -179,6 +180,7 @@ struct PolSwiGLU {
   const T *wg, *wu;
   int ldb, F;
   ActOut act;
+  uintptr_t weight_bits() const { return (uintptr_t)wg | (uintptr_t)wu; }
   __device__ __forceinline__ void b_ptrs(int t, int BN, const T*& lo, const T*& hi) const {
     lo = wg + (size_t)t * (BN / 2) * ldb;
     hi = wu + (size_t)t * (BN / 2) * ldb;
@@ -208,6 +210,7 @@ struct PolResid {
   const T* w;
   int ldb, N;
   float* resid;
+  uintptr_t weight_bits() const { return (uintptr_t)w; }
   __device__ __forceinline__ void b_ptrs(int t, int BN, const T*& lo, const T*& hi) const {
     lo = w + (size_t)t * BN * ldb;
     hi = lo + (size_t)(BN / 2) * ldb;
@@ -301,6 +304,7 @@ struct PolLMStats {
   LMParts part;
   float* logits;       // optional [M][ldc]
   int ldc;
+  uintptr_t weight_bits() const { return (uintptr_t)w; }
   __device__ __forceinline__ void b_ptrs(int t, int BN, const T*& lo, const T*& hi) const {
     lo = w + (size_t)t * BN * ldb;
     hi = lo + (size_t)(BN / 2) * ldb;
@@ -1230,15 +1234,25 @@ static hipError_t launch_bf16_bm(const Pol& pol, const ActIn& a, int M, int K, i
   return launch_bf16_pw<128, BN>(pol, a, M, K, N, S, pw, ws, st, reduce);
 }
 
+// Whether gemm_pp_kernel may take these operands: its copies put 16 bytes a
+// lane straight into LDS and want them aligned, as weights that are views into
+// a larger buffer need not be.  gemm_bf16_kernel loads into registers, from
+// any address.
+template <class Pol>
+static bool pp_aligned(const Pol& pol, const ActIn& a) {
+  return ((pol.weight_bits() | (uintptr_t)a.hi | (uintptr_t)a.lo) & 15) == 0;
+}
+
 // Launch plan of one projection: the configuration with a valid tile width
 // and the split-K factor.
 template <class Pol>
-static GemmCfg plan_bf16(const char* kind, const Pol& pol, int M, int K, int N, bool pair, GemmCfg c,
-                         const SplitWs& ws, int (*bn_ok)(const Pol&, int)) {
+static GemmCfg plan_bf16(const char* kind, const Pol& pol, const ActIn& a, int M, int K, int N,
+                         GemmCfg c, const SplitWs& ws, int (*bn_ok)(const Pol&, int)) {
   const GemmCfg given = c;
   c = cfg_override(kind, c);
   const bool overridden = c.bn != given.bn || c.s != given.s || c.pp != given.pp || c.bm != given.bm || c.pw != given.pw;
-  if (c.pp != 0 && !has_tile<Pol>::value && K % 64 == 0) {
+  const bool pair = a.lo != nullptr, pp_ok = K % 64 == 0 && pp_aligned(pol, a);
+  if (c.pp != 0 && pp_ok) {
     c.pp = pp_plan(pol, M, K, N, pair, ws.floats, bn_ok, c.pp, c.s);
     if (c.pp) return c;
   }
@@ -1255,7 +1269,7 @@ static GemmCfg plan_bf16(const char* kind, const Pol& pol, int M, int K, int N, 
   // tiles, 84 -> 71 us; down, 28 tiles in 2 splits, 95 -> 48 us).  At 0.8 the
   // estimate is not safe: several workgroups of this kernel may share a CU
   // (gate/up with the pair at 330 rows, 135 us, would move to 148)
-  if (!has_tile<Pol>::value && K % 64 == 0 && !overridden) {
+  if (pp_ok && !overridden) {
     const float us = (float)ceil_div(tiles * S, 256) *
                          (K / 64 / S * bf16_step_us(c.bn, c.bm, pair) + PP_FIXED_US) +
                      split_sum_us(M, N, S);
@@ -1308,7 +1322,7 @@ static hipError_t launch_plan(const Pol& pol, const ActIn& a, int M, int K, int 
 template <class Pol>
 static hipError_t run_bf16(const char* kind, Pol pol, const ActIn& a, int M, int K, int N,
                            GemmCfg c, SplitWs ws, hipStream_t st, int (*bn_ok)(const Pol&, int)) {
-  c = plan_bf16(kind, pol, M, K, N, a.lo != nullptr, c, ws, bn_ok);
+  c = plan_bf16(kind, pol, a, M, K, N, c, ws, bn_ok);
   return launch_plan(pol, a, M, K, N, c, ws, st);
 }
 
@@ -1494,8 +1508,7 @@ hipError_t gemm_resid(int dtype, const char* kind, const ActIn& a, int M, int K,
     if (e == hipSuccess && fuse) launch_resid_norm<float>(S, M, N, ws.part, resid, nrm, st);
   } else {
     PolResid<bf16_t> p{(const bf16_t*)w, K, N, resid};
-    const GemmCfg c = plan_bf16(kind, p, M, K, N, a.lo != nullptr,
-                                default_cfg(kind, M, a.lo != nullptr), ws,
+    const GemmCfg c = plan_bf16(kind, p, a, M, K, N, default_cfg(kind, M, a.lo != nullptr), ws,
                                 any_bn<PolResid<bf16_t>>);
     fuse = resid_norm_ok(c.s, N, nrm);
     e = launch_plan(p, a, M, K, N, c, ws, st, !fuse);
@@ -1595,7 +1608,7 @@ hipError_t lm_head_stats(const ActIn& a, int M, int K, const void* w, int N, int
   const float us1 = pp_cost(1, M, K, N, pair), us4 = pp_cost(4, M, K, N, pair);
   const float us = (float)ceil_div(N / 128 * ceil_div(M, 128), 256) *
                    (K / 64 * bf16_step_us(128, 128, pair) + PP_FIXED_US);
-  if (c.pp && N % 256 == 0 && (us1 < us4 ? us1 : us4) < us) {
+  if (c.pp && pp_aligned(p, a) && N % 256 == 0 && (us1 < us4 ? us1 : us4) < us) {
     e = us1 < us4
             ? launch_pp<256, 256, 2, 4>(p, a, M, K, N, 1, none, st, false)
             : launch_pp<128, 256, 2, 4>(p, a, M, K, N, 1, none, st, false);

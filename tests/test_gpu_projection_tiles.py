@@ -32,12 +32,26 @@ def _shape(dims, base=LLADA_8B):
     return dataclasses.replace(base, name="tiles", n_layers=1, vocab=512, mask_id=511, **dims)
 
 
-def _layer(shape, rows, pair, first_out):
-    """(x, GPU hidden, GPU keys, oracle hidden, oracle keys) of one layer."""
+def _view(t):
+    """The same values 8 bytes into a larger buffer."""
+    n = 8 // t.element_size()
+    v = torch.empty(t.numel() + n, dtype=t.dtype, device=t.device)[n:].view(t.shape)
+    return v.copy_(t)
+
+
+def _layer(shape, rows, pair, first_out, views=False):
+    """(x, GPU hidden, GPU keys, oracle hidden, oracle keys) of one layer; with
+    `views`, all its weights lie at addresses that 16 does not divide."""
     from paper_2608_23167_amd import _lib as L
     from paper_2608_23167_amd import api
     from paper_2608_23167_amd.model import DeviceKVCache, DeviceModel
     w = make_weights(shape, seed=3, device="cuda", norm_jitter=0.1)
+    if views:
+        for holder in (w, w.layers[0]):
+            for name, t in vars(holder).items():
+                if torch.is_tensor(t):
+                    setattr(holder, name, _view(t))
+        assert all(t.data_ptr() % 16 for t in w.layers[0].tensors())
     m = DeviceModel(shape, w, pair_layers=1 if pair else 0)
     x = seeded_normal((1, rows, shape.d_model), 4, "tiles.x", device="cuda")
     pos = torch.arange(rows, dtype=torch.int32, device="cuda")
@@ -66,6 +80,15 @@ def _worst(a, b):
     return float(np.max(np.linalg.norm(a - b, axis=1) / np.linalg.norm(b, axis=1)))
 
 
+def _check(shape, rows, pair, **kw):
+    x, hidden, keys, ref, ref_k = _layer(shape, rows, pair, max(rows - 40, 0), **kw)
+    assert np.isfinite(hidden).all()
+    e, ek = _worst(hidden - x, ref - x), _worst(keys, ref_k)
+    print(f"rows {rows} pair {pair}: branch {e:.2e}, keys {ek:.2e}")
+    assert e < (3e-3 if pair else 1e-2)
+    assert ek < (1e-3 if pair else 5e-3)
+
+
 @pytest.mark.parametrize("dims,rows,pair", [
     (WIDE, 256, False), (WIDE, 257, False), (WIDE, 385, True), (WIDE, 511, False),
     (WIDE, 513, True), (WIDE, 1025, False), (WIDE, 1776, False), (WIDE, 1776, True),
@@ -77,13 +100,14 @@ def test_layer_at_tile_edges(dims, rows, pair):
     float16 attention operands in a chain: 1e-2 of the branch (hidden - x),
     which has no share of the exact residual; with the pair the float16
     operands alone remain: 3e-3.  Keys pass one projection: 5e-3."""
-    shape = _shape(dims)
-    x, hidden, keys, ref, ref_k = _layer(shape, rows, pair, rows - 40)
-    assert np.isfinite(hidden).all()
-    e, ek = _worst(hidden - x, ref - x), _worst(keys, ref_k)
-    print(f"rows {rows} pair {pair}: branch {e:.2e}, keys {ek:.2e}")
-    assert e < (3e-3 if pair else 1e-2)
-    assert ek < (1e-3 if pair else 5e-3)
+    _check(_shape(dims), rows, pair)
+
+
+@pytest.mark.parametrize("rows,pair", [(40, False), (300, False), (513, True)])
+def test_weights_that_are_views(rows, pair):
+    """Weights 8 bytes into a larger buffer, at row counts where aligned ones go
+    straight into LDS 16 bytes at a time: the bounds of test_layer_at_tile_edges."""
+    _check(_shape(WIDE), rows, pair, views=True)
 
 
 @pytest.mark.parametrize("dims", F32)
