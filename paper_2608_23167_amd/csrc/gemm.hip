@@ -1263,19 +1263,26 @@ static GemmCfg plan_bf16(const char* kind, const Pol& pol, const ActIn& a, int M
   const int tiles = (N / c.bn) * ceil_div(M, c.bm);
   int S = c.s > 0 ? c.s : auto_split(tiles, M, K, ws.floats, N);
   while (S > 1 && (K % (256 * S) != 0 || (size_t)S * M * N > ws.floats)) S /= 2;
-  // widths that leave this kernel with few workgroups or a nearly empty last
-  // round: gemm_pp_kernel, whose splits need not divide K, if it should take
-  // less than 0.7 of the time (grouped-query shape at 120 rows: gate/up, 296
-  // tiles, 84 -> 71 us; down, 28 tiles in 2 splits, 95 -> 48 us).  At 0.8 the
-  // estimate is not safe: several workgroups of this kernel may share a CU
-  // (gate/up with the pair at 330 rows, 135 us, would move to 148)
+  // below 512 rows gemm_pp_kernel, whose splits need not divide K, where it
+  // should take less time than this kernel: in one pass from 257 rows as soon
+  // as the estimates say so (8B shape, 300 rows: 234 -> 225 us a layer; at
+  // d = 512, 351 rows, where they do not, it would be 182 -> 188 us for two
+  // layers).  Elsewhere at less than 0.7 of it: widths that leave this kernel
+  // with few workgroups or a nearly empty last round (grouped-query shape at
+  // 120 rows: gate/up, 296 tiles, 84 -> 71 us; down, 28 tiles in 2 splits, 95
+  // -> 48 us; QKV with the pair at 352 rows, 50 -> 43 us; 8B gate/up with the
+  // pair at 440 rows, 165 -> 152 us).  At 0.8 the estimate is not safe there:
+  // several workgroups of this kernel may share a CU (with the pair, 8B
+  // gate/up at 330 rows, 131 us, would move to 149; QKV at 376 rows, 94 us, to
+  // 100; grouped-query gate/up at 440 rows, 231 us, to 282)
   if (pp_ok && !overridden) {
     const float us = (float)ceil_div(tiles * S, 256) *
                          (K / 64 / S * bf16_step_us(c.bn, c.bm, pair) + PP_FIXED_US) +
                      split_sum_us(M, N, S);
+    const float margin = !pair && M > 256 ? 1.0f : 0.7f;
     int ps = 0;
     const int tile = pp_plan(pol, M, K, N, pair, ws.floats, bn_ok, -1, ps);
-    if (tile && pp_cost(tile, M, K, N, pair, ps) < 0.7f * us) {
+    if (tile && pp_cost(tile, M, K, N, pair, ps) < margin * us) {
       c.pp = tile;
       c.s = ps;
       return c;
@@ -1433,17 +1440,19 @@ static hipError_t run_f32(const Pol& pol, const ActIn& a, int M, int K, int N, S
   return hipGetLastError();
 }
 
-// Default launch choices: the cached-step row counts (M <= 256) are
-// HBM-bound and want every CU streaming weights; more rows are MFMA-bound and
-// take gemm_pp_kernel.  `paired`: the activations carry the lo part (twice the
-// MFMA work per weight byte).  Measured choices (8B shape, us per layer over
-// the four projections with their sums, gemm_bf16_kernel / gemm_pp_kernel):
-//  * gemm_pp_kernel from 257 rows in one pass (240 rows 173 / 197, 300 rows 234 /
-//    225, 376 rows 245 / 225, 504 rows 279 / 238), from 385 rows with the pair
-//    (300 rows 353 / 381, 376 rows 393 / 387, 440 rows 423 / 403, 504 rows 464 /
-//    414);
+// Default launch choices: the cached-step row counts are HBM-bound and want
+// every CU streaming weights; many rows are MFMA-bound and take
+// gemm_pp_kernel.  `paired`: the activations carry the lo part (twice the MFMA
+// work per weight byte).  Measured choices:
+//  * gemm_pp_kernel for every projection from 512 rows, below by estimate
+//    (plan_bf16).  8B shape, us per layer, the four projections on
+//    gemm_bf16_kernel / on gemm_pp_kernel: one pass 240 rows 173 / 197, 300
+//    rows 234 / 225, 376 rows 245 / 225, 504 rows 279 / 238.  Whole layers with
+//    the pair, all on gemm_bf16_kernel / gate/up alone on gemm_pp_kernel / all
+//    on it: 300 rows 359 / 381 / 407, 376 rows 401 / 406 / 422, 400 rows 408 /
+//    402 / 436, 440 rows 420 / 406 / 435, 511 rows 465 / 433 / 449;
 //  * row tiles of gemm_bf16_kernel: 128 rows, except 256 for the one-pass
-//    gate/up from 129 rows (one row tile instead of two); 64- and 192-row
+//    gate/up from 129 to 256 rows (one row tile instead of two); 64- and 192-row
 //    tiles and the 256-row tiles elsewhere measured slower;
 //  * QKV: 96-column tiles (128 column tiles at d = 4096 with 32 + 2 x 32 heads:
 //    with the automatic split-K, 2 ways up to 128 rows, 256 workgroups where
@@ -1459,11 +1468,11 @@ static hipError_t run_f32(const Pol& pol, const ActIn& a, int M, int K, int N, S
 //    8-way split.
 static GemmCfg default_cfg(const char* kind, int M, bool paired) {
   if (!strcmp(kind, "lm")) return GemmCfg{128, 1, 4, M > 128 ? -1 : 0};
-  if (M > (paired ? (!strcmp(kind, "qkv") ? 352 : 384) : 256)) return GemmCfg{128, 0, 4, -1};
+  if (M > 511) return GemmCfg{128, 0, 4, -1};
   if (!strcmp(kind, "qkv")) return GemmCfg{96, 0, 4, 0};
   if (!strcmp(kind, "gate_up")) {
     GemmCfg c{96, 1, 4, 0};
-    if (!paired && M > 128) c.bm = 256;   // one row tile: 9% faster at 240 rows
+    if (!paired && M > 128 && M <= 256) c.bm = 256;   // one row tile: 9% faster at 240 rows
     return c;
   }
   if (!strcmp(kind, "o") && M <= 128) return GemmCfg{64, 4, 4, 0};
@@ -1593,31 +1602,78 @@ size_t lm_stats_ws_bytes(int M, int N) {
   return (size_t)M * (N / 64) * (sizeof(LMHead) + sizeof(LMTail));
 }
 
+// Launch plan of the LM head: 256-column tiles of one or two groups of 128
+// rows, whichever takes less time; a small vocabulary has too few of them
+// (2048 ids, 240 rows: 50 us on 128-column tiles, 68 on these).
+static GemmCfg lm_plan(const PolLMStats<bf16_t>& p, const ActIn& a, int M, int K, int N) {
+  const bool pair = a.lo != nullptr;
+  GemmCfg c = cfg_override("lm", default_cfg("lm", M, pair));
+  const float us1 = pp_cost(1, M, K, N, pair), us4 = pp_cost(4, M, K, N, pair);
+  const float us = (float)ceil_div(N / 128 * ceil_div(M, 128), 256) *
+                   (K / 64 * bf16_step_us(128, 128, pair) + PP_FIXED_US);
+  if (c.pp && pp_aligned(p, a) && N % 256 == 0 && (us1 < us4 ? us1 : us4) < us) c.pp = us1 < us4 ? 1 : 4;
+  else c.pp = 0;
+  return c;
+}
+
 hipError_t lm_head_stats(const ActIn& a, int M, int K, const void* w, int N, int mask_id, int k,
                          void* stats_ws, float* logits, int32_t* argmax, float* conf,
                          int32_t* topk_ids, float* topk_w, hipStream_t st) {
   LMParts parts{(LMHead*)stats_ws, (LMTail*)((LMHead*)stats_ws + (size_t)M * (N / 64)), N / 64};
   PolLMStats<bf16_t> p{(const bf16_t*)w, K, N, mask_id, parts, logits, N};
-  const GemmCfg c = cfg_override("lm", default_cfg("lm", M, a.lo != nullptr));
+  const GemmCfg c = lm_plan(p, a, M, K, N);
   const SplitWs none{nullptr, 0};
   hipError_t e;
-  // one or two groups of 128 rows per tile, whichever takes less time; a small
-  // vocabulary has too few 256-column tiles (2048 ids, 240 rows: 50 us on
-  // 128-column tiles, 68 on these)
-  const bool pair = a.lo != nullptr;
-  const float us1 = pp_cost(1, M, K, N, pair), us4 = pp_cost(4, M, K, N, pair);
-  const float us = (float)ceil_div(N / 128 * ceil_div(M, 128), 256) *
-                   (K / 64 * bf16_step_us(128, 128, pair) + PP_FIXED_US);
-  if (c.pp && pp_aligned(p, a) && N % 256 == 0 && (us1 < us4 ? us1 : us4) < us) {
-    e = us1 < us4
-            ? launch_pp<256, 256, 2, 4>(p, a, M, K, N, 1, none, st, false)
-            : launch_pp<128, 256, 2, 4>(p, a, M, K, N, 1, none, st, false);
-  } else {
-    e = launch_bf16_pw<128, 128>(p, a, M, K, N, 1, c.pw, none, st, true);
-  }
+  if (c.pp == 1) e = launch_pp<256, 256, 2, 4>(p, a, M, K, N, 1, none, st, false);
+  else if (c.pp == 4) e = launch_pp<128, 256, 2, 4>(p, a, M, K, N, 1, none, st, false);
+  else e = launch_bf16_pw<128, 128>(p, a, M, K, N, 1, c.pw, none, st, true);
   if (e != hipSuccess) return e;
   launch(lm_merge_kernel, dim3(M), dim3(256), 0, st, parts, k, argmax, conf, topk_ids, topk_w);
   return hipGetLastError();
 }
 
 }  // namespace ssm
+
+#ifdef SSM_DEBUG
+// The launch that a projection of a bfloat16 model takes (debug library only,
+// for tests of the dispatch): kind is qkv, o, gate_up, down or lm, `weights`
+// stands for the address of its weights.  out: 1 for gemm_pp_kernel or 0 for
+// gemm_bf16_kernel, tile rows, tile columns, K splits.
+extern "C" int32_t ssm_debug_gemm_plan(const char* kind, int32_t M, int32_t d, int32_t H,
+                                       int32_t Hkv, int32_t F, int32_t V, int32_t pair,
+                                       uint64_t weights, int32_t* out) {
+  using namespace ssm;
+  const bf16_t* w = (const bf16_t*)(uintptr_t)weights;
+  const ActIn a{nullptr, pair ? (const bf16_t*)256 : nullptr, d, row_groups(M)};
+  const int dh = d / H, nq = (H + 2 * Hkv) * dh;
+  int maxn = nq > 2 * F ? nq : 2 * F;
+  if (V > maxn) maxn = V;
+  const SplitWs ws{nullptr, gemm_split_ws_floats(M, maxn)};
+  const GemmCfg given = default_cfg(kind, M, pair != 0);
+  GemmCfg c;
+  if (!strcmp(kind, "qkv")) {
+    PolQKV<bf16_t, f16_t> p{};
+    p.wq = p.wk = p.wv = w;
+    p.H = H; p.Hkv = Hkv; p.dh = dh;
+    c = plan_bf16(kind, p, a, M, d, nq, given, ws, qkv_bn);
+  } else if (!strcmp(kind, "gate_up")) {
+    PolSwiGLU<bf16_t> p{};
+    p.wg = p.wu = w;
+    c = plan_bf16(kind, p, a, M, d, 2 * F, given, ws, any_bn<PolSwiGLU<bf16_t>>);
+  } else if (!strcmp(kind, "lm")) {
+    PolLMStats<bf16_t> p{};
+    p.w = w;
+    c = lm_plan(p, a, M, d, V);
+    if (!c.pp) c.bn = 128;
+  } else {
+    PolResid<bf16_t> p{};
+    p.w = w;
+    c = plan_bf16(kind, p, a, M, !strcmp(kind, "down") ? F : d, d, given, ws, any_bn<PolResid<bf16_t>>);
+  }
+  out[0] = c.pp != 0;
+  out[1] = c.pp ? PP_TILES[c.pp - 1].bm : c.bm;
+  out[2] = c.pp ? PP_TILES[c.pp - 1].bn : c.bn;
+  out[3] = c.s;
+  return 0;
+}
+#endif
