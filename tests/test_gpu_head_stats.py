@@ -1,7 +1,8 @@
 """Row statistics of the LM head against the logits of the same call: ids in
 order (larger logit, then lower id), confidence and renormalised weights, at the
 edges of the row tiles, for vocabularies that do and do not divide into the
-column tiles, with ties within and across the 64-column segments.
+column tiles, with ties within and across the 64-column segments, on every
+kernel that the head may take (test_projection_plan.py asks for it).
 """
 import dataclasses
 
@@ -13,8 +14,9 @@ from synthetic import LLADA_8B, TINY, make_weights, seeded_normal
 pytestmark = pytest.mark.gpu
 
 
-def _head(base, rows, vocab, k, mask_id):
-    """(logits, argmax, conf, ids, weights) of a model without layers."""
+def _head(base, rows, vocab, k, mask_id, pair):
+    """(logits, argmax, conf, ids, weights) of a model without layers; `pair`: the
+    head multiplies both parts of the bfloat16 pair."""
     from paper_2608_23167_amd import _lib as L
     from paper_2608_23167_amd import api
     from paper_2608_23167_amd.model import DeviceKVCache, DeviceModel
@@ -26,7 +28,7 @@ def _head(base, rows, vocab, k, mask_id):
     w.lm_head[2 * n:2 * n + 9] = 0                       # and nine zeros
     x = seeded_normal((1, rows, shape.d_model), 6, "head.x", device="cuda")
     x[0, 0] = 0                                          # a row of equal logits
-    m = DeviceModel(shape, w)
+    m = DeviceModel(shape, w, act_mode=L.SSM_ACT_BF16X2 if pair else L.SSM_ACT_BF16)
     cache = DeviceKVCache(dataclasses.replace(shape, n_layers=1), 1, rows)
     out = (torch.zeros(rows, dtype=torch.int32, device="cuda"), torch.zeros(rows, device="cuda"),
            torch.zeros(rows * k, dtype=torch.int32, device="cuda"), torch.zeros(rows * k, device="cuda"))
@@ -43,15 +45,25 @@ def _head(base, rows, vocab, k, mask_id):
             out[2].view(rows, k).cpu(), out[3].view(rows, k).cpu())
 
 
-@pytest.mark.parametrize("base,rows,vocab,k,mask_id", [
-    (LLADA_8B, 1, 128, 8, 127), (LLADA_8B, 63, 384, 5, 0), (LLADA_8B, 128, 1024, 8, 1000),
-    (LLADA_8B, 129, 1024, 8, 64), (LLADA_8B, 129, 640, 1, 639), (LLADA_8B, 257, 2048, 5, 2047),
-    (LLADA_8B, 300, 20480, 8, 700), (LLADA_8B, 120, 40960, 8, 40959),
-    (TINY, 33, 32, 8, 31), (TINY, 100, 4096, 5, 77)])
-def test_statistics_follow_the_logits(base, rows, vocab, k, mask_id):
+# (base, rows, vocabulary, k, mask id, pair): the last rows of a 256-row tile, its
+# second 128 rows and a second tile, with one part of the operand and with two
+HEADS = [
+    (LLADA_8B, 1, 128, 8, 127, False), (LLADA_8B, 63, 384, 5, 0, False),
+    (LLADA_8B, 128, 1024, 8, 1000, False), (LLADA_8B, 129, 1024, 8, 64, False),
+    (LLADA_8B, 129, 640, 1, 639, False), (LLADA_8B, 257, 2048, 5, 2047, False),
+    (LLADA_8B, 300, 20480, 8, 700, False), (LLADA_8B, 120, 40960, 8, 40959, False),
+    (LLADA_8B, 129, 40960, 8, 40959, False), (LLADA_8B, 240, 40960, 5, 27000, False),
+    (LLADA_8B, 257, 32768, 8, 32767, False), (LLADA_8B, 300, 32768, 5, 0, False),
+    (LLADA_8B, 120, 1024, 8, 1000, True), (LLADA_8B, 300, 20480, 8, 700, True),
+    (LLADA_8B, 300, 32768, 8, 32767, True),
+    (TINY, 33, 32, 8, 31, False), (TINY, 100, 4096, 5, 77, False)]
+
+
+@pytest.mark.parametrize("base,rows,vocab,k,mask_id,pair", HEADS)
+def test_statistics_follow_the_logits(base, rows, vocab, k, mask_id, pair):
     """Ids are exact.  The sum of up to 4e4 float32 exponentials, in parts, is
     off by a few hundred roundings at most: 5e-5."""
-    logits, argmax, conf, ids, w = _head(base, rows, vocab, k, mask_id)
+    logits, argmax, conf, ids, w = _head(base, rows, vocab, k, mask_id, pair)
     z = logits.clone()
     z[:, mask_id] = -float("inf")
     order = torch.sort(z, dim=1, descending=True, stable=True)

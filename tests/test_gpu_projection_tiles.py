@@ -1,7 +1,7 @@
 """The projection kernels at the edges of their tiles: one decoder layer over
 row counts just above and below whole row tiles, at widths that make the
-launcher choose each tile shape and split-K factor, against the oracle's layer
-in float64.
+launcher choose each tile shape and split-K factor (test_projection_plan.py
+asks it), against the oracle's layer in float64.
 """
 from types import SimpleNamespace
 
@@ -18,6 +18,30 @@ pytestmark = pytest.mark.gpu
 # forward 2F divisible by 192 and 256
 WIDE = dict(d_model=1024, n_heads=8, n_kv_heads=8, ffn_dim=3072)
 GROUPED = dict(d_model=768, n_heads=6, n_kv_heads=2, ffn_dim=6144)
+# the widths of the 7B shape, where launches of up to 256 rows take gemm_pp_kernel
+WIDTHS_7B = dict(d_model=3584, n_heads=28, n_kv_heads=4, ffn_dim=18944)
+
+
+def _dims(d, kv, ffn):
+    return dict(d_model=d, n_heads=d // 128, n_kv_heads=kv, ffn_dim=ffn)
+
+
+# (widths, rows, pair): row tiles, the small-row launches and, on widths that
+# are quick to check, every split-K factor of gemm_pp_kernel
+CASES = [
+    (WIDE, 256, False), (WIDE, 257, False), (WIDE, 385, True), (WIDE, 511, False),
+    (WIDE, 513, True), (WIDE, 1025, False), (WIDE, 1776, False), (WIDE, 1776, True),
+    (GROUPED, 300, False), (GROUPED, 513, False), (GROUPED, 1025, True), (GROUPED, 1281, False),
+    (WIDTHS_7B, 1, False), (WIDTHS_7B, 16, False), (WIDTHS_7B, 120, False),
+    (WIDTHS_7B, 240, False), (WIDTHS_7B, 256, False),
+    (WIDTHS_7B, 16, True), (WIDTHS_7B, 120, True), (WIDTHS_7B, 300, True),
+    (_dims(256, 1, 1280), 1, False), (_dims(256, 1, 1280), 1, True), (_dims(256, 1, 8448), 257, True),
+    (_dims(512, 1, 256), 513, True), (_dims(768, 1, 256), 513, True), (_dims(1024, 1, 256), 513, False),
+    (_dims(1024, 1, 2304), 256, False), (_dims(1280, 1, 768), 200, False),
+    (_dims(1280, 1, 4864), 1, True), (_dims(1536, 1, 256), 513, False), (_dims(1536, 1, 7424), 1, True),
+    (_dims(1792, 14, 256), 1, False), (_dims(1792, 1, 2816), 1, False), (_dims(1792, 1, 3840), 1, True),
+    (_dims(2048, 1, 2816), 257, False), (_dims(2048, 1, 5376), 257, True),
+    (_dims(2560, 1, 1280), 200, False), (_dims(2560, 1, 5376), 1025, True)]
 
 
 # float32 models: K columns that leave a rest of 32, 64 or 96 to whole trips of
@@ -89,10 +113,7 @@ def _check(shape, rows, pair, **kw):
     assert ek < (1e-3 if pair else 5e-3)
 
 
-@pytest.mark.parametrize("dims,rows,pair", [
-    (WIDE, 256, False), (WIDE, 257, False), (WIDE, 385, True), (WIDE, 511, False),
-    (WIDE, 513, True), (WIDE, 1025, False), (WIDE, 1776, False), (WIDE, 1776, True),
-    (GROUPED, 300, False), (GROUPED, 513, False), (GROUPED, 1025, True), (GROUPED, 1281, False)])
+@pytest.mark.parametrize("dims,rows,pair", CASES)
 def test_layer_at_tile_edges(dims, rows, pair):
     """Per row, because an error at a tile edge touches a few rows only.  Bounds:
     a one-pass projection rounds its input to bfloat16 (2^-9 of each element at

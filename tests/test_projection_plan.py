@@ -25,6 +25,31 @@ def plan(kind, rows, dims, pair=False, weights=0):
     return tuple(out)
 
 
+TILES = {(256, 256), (256, 192), (256, 128), (128, 256), (128, 192)}
+
+
+@pytest.mark.parametrize("pair", [False, True])
+def test_gpu_cases_reach_every_launch(pair):
+    """The layers that the GPU compares with the oracle take every tile shape of
+    gemm_pp_kernel, its splits 1 to 8, and gemm_bf16_kernel."""
+    from test_gpu_projection_tiles import CASES
+    seen = set()
+    for dims, rows, p in CASES:
+        if p == pair:
+            args = (dims["d_model"], dims["n_heads"], dims["n_kv_heads"], dims["ffn_dim"], 512)
+            seen |= {plan(kind, rows, args, pair) for kind in KINDS[:4]}
+    assert {s[1:3] for s in seen if s[0]} == TILES
+    assert {s[3] for s in seen if s[0]} == set(range(1, 9))
+    assert any(not s[0] for s in seen)
+
+
+def test_gpu_cases_reach_every_head_launch():
+    from test_gpu_head_stats import HEADS
+    seen = {(pair, *plan("lm", rows, (512, 4, 4, 512, vocab), pair)[:3])
+            for base, rows, vocab, _, _, pair in HEADS if base.dtype == "bf16"}
+    assert seen == {(p, *t) for p in (False, True) for t in ((0, 128, 128), (1, 256, 256), (1, 128, 256))}
+
+
 @pytest.mark.parametrize("dims", [LLADA, DREAM, GQA_8, SMALL])
 def test_unaligned_weights_go_through_registers(dims):
     for kind in KINDS:
