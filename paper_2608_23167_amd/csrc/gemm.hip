@@ -109,23 +109,6 @@ struct PolQKV {
     lo = b_row(t, BN, 0);
     hi = lo + (size_t)(dh / 2) * ldb;
   }
-  __device__ __forceinline__ void store(int m, int t, int c, int BN, float vlo, float vhi) const {
-    const int half = dh / 2, j = t * (BN / 2) + c, head = j / half, i = j - head * half;
-    const int s = m / n_rows, row = m % n_rows;
-    if (head < H + Hkv) {
-      const float2 cs = rope[((size_t)(rope_per_seq ? s : 0) * n_rows + row) * half + i];
-      const float a = vlo * cs.x - vhi * cs.y;
-      const float b = vhi * cs.x + vlo * cs.y;
-      vlo = a;
-      vhi = b;
-    }
-    TO* dst;
-    if (head < H) dst = q + (((size_t)s * H + head) * n_rows + row) * dh;
-    else if (head < H + Hkv) dst = kc + (((size_t)s * Hkv + (head - H)) * cap + n_cached + row) * dh;
-    else dst = vc + (((size_t)s * Hkv + (head - H - Hkv)) * cap + n_cached + row) * dh;
-    stf(dst + i, vlo);
-    stf(dst + i + half, vhi);
-  }
   // columns c0 .. c0 + 7 of both halves (c0 a multiple of 8: one head)
   __device__ __forceinline__ void store8(int m, int t, int c0, int BN, const float (&vlo)[8],
                                          const float (&vhi)[8]) const {
@@ -185,10 +168,6 @@ struct PolSwiGLU {
     lo = wg + (size_t)t * (BN / 2) * ldb;
     hi = wu + (size_t)t * (BN / 2) * ldb;
   }
-  __device__ __forceinline__ void store(int m, int t, int c, int BN, float g, float u) const {
-    const float silu = g / (1.0f + expf(-g));
-    act.store<T>(m, t * (BN / 2) + c, silu * u);
-  }
   __device__ __forceinline__ void store8(int m, int t, int c0, int BN, const float (&g)[8],
                                          const float (&u)[8]) const {
     float v[8];
@@ -215,9 +194,6 @@ struct PolResid {
     lo = w + (size_t)t * BN * ldb;
     hi = lo + (size_t)(BN / 2) * ldb;
   }
-  __device__ __forceinline__ void store1(int m, int n, float v) const {
-    resid[(size_t)m * N + n] += v;
-  }
   __device__ __forceinline__ void store8_1(int m, int n0, const float (&v)[8]) const {
     float4* p = (float4*)(resid + (size_t)m * N + n0);
     float4 a = p[0], b = p[1];
@@ -241,9 +217,6 @@ struct PolStore {
   __device__ __forceinline__ void b_ptrs(int t, int BN, const T*& lo, const T*& hi) const {
     lo = w + (size_t)t * BN * ldb;
     hi = lo + (size_t)(BN / 2) * ldb;
-  }
-  __device__ __forceinline__ void store1(int m, int n, float v) const {
-    c[(size_t)m * ldc + n] = v;
   }
   __device__ __forceinline__ void store8_1(int m, int n0, const float (&v)[8]) const {
     store_row8(c + (size_t)m * ldc + n0, v);
@@ -1211,26 +1184,35 @@ template <int BM, int BN, class Pol>
 static hipError_t launch_bf16_pw(const Pol& pol, const ActIn& a, int M, int K, int N, int S,
                                  int pw, SplitWs ws, hipStream_t st, bool reduce) {
   const bool split = a.lo != nullptr;
+#ifdef SSM_TUNING
   // the staging loop is unrolled by the ring depth: nk = K / S / 64 must be a
   // multiple of it (of 4 always, host-checked)
   if (pw >= 8 && (K / S / 64) % 8 == 0)
     return split ? launch_bf16<BM, BN, 8, true>(pol, a, M, K, N, S, ws, st, reduce)
                  : launch_bf16<BM, BN, 8, false>(pol, a, M, K, N, S, ws, st, reduce);
+#endif
   return split ? launch_bf16<BM, BN, 4, true>(pol, a, M, K, N, S, ws, st, reduce)
                : launch_bf16<BM, BN, 4, false>(pol, a, M, K, N, S, ws, st, reduce);
 }
 
-// Row tile of gemm_bf16_kernel: 128 (default), 64 (two row tiles share each
-// weight tile through L2 on small row counts), 192 or 256 (one-pass layers,
-// tiles up to 96 columns: the register budget of a compute wave).
+// Row tile of gemm_bf16_kernel: 128, or 256 for the one-pass gate/up on
+// 96-column tiles (the register budget of a compute wave).  A tuning build has
+// more: 64 (two row tiles share each weight tile through L2 on small row
+// counts), and 192 and 256 for every one-pass projection on up to 96 columns.
 template <int BN, class Pol>
 static hipError_t launch_bf16_bm(const Pol& pol, const ActIn& a, int M, int K, int N, int S,
                                  int pw, int bm, SplitWs ws, hipStream_t st, bool reduce) {
+  const bool one_pass = a.lo == nullptr;
+#ifdef SSM_TUNING
+  constexpr bool ROWS_256 = BN <= 96;
   if (bm == 64) return launch_bf16_pw<64, BN>(pol, a, M, K, N, S, pw, ws, st, reduce);
-  if constexpr (BN <= 96) {
-    if (bm == 192 && a.lo == nullptr) return launch_bf16_pw<192, BN>(pol, a, M, K, N, S, pw, ws, st, reduce);
-    if (bm == 256 && a.lo == nullptr) return launch_bf16_pw<256, BN>(pol, a, M, K, N, S, pw, ws, st, reduce);
-  }
+  if constexpr (BN <= 96)
+    if (bm == 192 && one_pass) return launch_bf16<192, BN, 4, false>(pol, a, M, K, N, S, ws, st, reduce);
+#else
+  constexpr bool ROWS_256 = BN == 96 && std::is_same<Pol, PolSwiGLU<bf16_t>>::value;
+#endif
+  if constexpr (ROWS_256)
+    if (bm == 256 && one_pass) return launch_bf16<256, BN, 4, false>(pol, a, M, K, N, S, ws, st, reduce);
   return launch_bf16_pw<128, BN>(pol, a, M, K, N, S, pw, ws, st, reduce);
 }
 
