@@ -1553,9 +1553,6 @@ __global__ void __launch_bounds__(256) lm_merge_kernel(LMParts part, int k,
       if (h[c].y > 0.f) {
         if (h[c].x > m) { s = s * expf(m - h[c].x) + h[c].y; m = h[c].x; }
         else s += h[c].y * expf(h[c].x - m);
-      } else if (h[c].x > m) {                   // no finite sum: its maximum alone
-        s *= expf(m - h[c].x);
-        m = h[c].x;
       }
       if (stat_better(h[c].z, __float_as_int(h[c].w), v, i)) { v = h[c].z; i = __float_as_int(h[c].w); }
     }

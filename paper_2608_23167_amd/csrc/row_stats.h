@@ -38,11 +38,12 @@ __device__ __forceinline__ float ordered_float(int o) {
   return __int_as_float(o ^ ((o >> 31) & 0x7fffffff));
 }
 
-// (max, sum of exp(x - max)) pairs: s == 0 adds nothing to a sum, but its
-// maximum counts.  Two pairs that meet at an infinite maximum give NaN.
+// (max, sum of exp(x - max)) pairs: s == 0 is an empty one.
 __device__ __forceinline__ void stat_combine(float& m, float& s, float om, float os) {
+  if (!(os > 0.f)) return;
+  if (!(s > 0.f)) { m = om; s = os; return; }
   const float M = fmaxf(m, om);
-  s = (s == 0.f ? 0.f : s * expf(m - M)) + (os == 0.f ? 0.f : os * expf(om - M));
+  s = s * expf(m - M) + os * expf(om - M);
   m = M;
 }
 
@@ -65,7 +66,6 @@ __device__ __forceinline__ void row_stats_end(RowStatShared& sh, float m, float 
                                               int row, int k, int32_t* argmax, float* conf,
                                               int32_t* topk_ids, float* topk_w, Fill fill) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  if (!(s > 0.f)) s = 0.f;    // empty, or NaN among its values
   // id STAT_NONE sorts last among -inf
   const long long key = ((long long)ordered_bits(v) << 32) | (unsigned)(STAT_NONE - i);
   sh.key[tid] = key;
@@ -117,7 +117,9 @@ __device__ __forceinline__ void row_stats_end(RowStatShared& sh, float m, float 
     float M = sh.m[0], S = sh.s[0];
     for (int w = 1; w < 4; ++w) stat_combine(M, S, sh.m[w], sh.s[w]);
     argmax[row] = sh.bi[0];
-    conf[row] = 1.0f / S;   // exp(max - max) / sum exp(x - max)
+    // exp(max - max) / sum exp(x - max): NaN for a best value of +inf, whose
+    // share of the partial sums stat_combine drops (inf - inf)
+    conf[row] = (sh.bv[0] == INFINITY ? __builtin_nanf("") : 1.0f) / S;
     float e[STAT_K], z = 0.f;
 #pragma unroll
     for (int q = 0; q < STAT_K; ++q) {
