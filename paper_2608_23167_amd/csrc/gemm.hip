@@ -28,12 +28,13 @@
 //   SwiGLU : gate row j and up row j -> silu(g) * u, written as the next
 //            projection's activation (pair);
 //   resid  : plain rows -> residual stream += value;
-//   LM head: per-row softmax statistics of each half tile (merged later).
+//   LM head: per-row softmax statistics of every 64 columns (merged later).
 // Split-K writes float32 partial tiles that a second kernel sums in a fixed
 // order before applying the same epilogue.
 //
 // gemm_bf16_kernel above serves the row counts that are bound by the weight
-// stream; gemm_pp_kernel, below, the row counts that are bound by the MFMAs.
+// stream; gemm_pp_kernel, below, the row counts that are bound by the MFMAs and
+// the smaller launches whose widths leave the first one few workgroups.
 #include <stdio.h>
 #include <stdlib.h>
 #include <string.h>
@@ -1041,7 +1042,10 @@ static int gemm_krot() {
 #endif
 }
 
-// Split-K is only used while S * M stays small, which bounds the workspace.
+// Float32 partials: the workspace holds SPLIT_ROWS_MAX rows of the widest
+// output (the vocabulary included).  gemm_bf16_kernel and the float32 kernel
+// split K while S * M stays within SPLIT_ROWS_MAX, gemm_pp_kernel while the S * M
+// rows of the projection's own width fit (O and down at 1127 rows: 2 splits).
 static constexpr int SPLIT_ROWS_MAX = 1024;
 size_t gemm_split_ws_floats(int M, int max_n) {
   (void)M;
@@ -1441,10 +1445,11 @@ static hipError_t run_f32(const Pol& pol, const ActIn& a, int M, int K, int N, S
 //    128-column tiles left 64 CUs idle);
 //  * gate/up: 96-column tiles (one workgroup per CU at 2F = 24576; the planner
 //    falls back to 128 where 96 does not divide 2F);
-//  * LM head: gemm_pp_kernel on 256-column tiles from 129 rows (126464 ids: 120
-//    rows 218 / 211, 240 rows 370 / 297, 480 rows 651 / 494; 152064 ids: 120 rows
-//    249 / 268, 240 rows 407 / 358), which halves the activation reads per weight
-//    read; below that the smaller tiles' last round is fuller;
+//  * LM head: gemm_pp_kernel on 256-column tiles from 129 rows, where the
+//    vocabulary has enough of them (lm_plan; 126464 ids: 120 rows 218 / 211, 240
+//    rows 370 / 297, 480 rows 651 / 494; 152064 ids: 120 rows 249 / 268, 240 rows
+//    407 / 358), which halves the activation reads per weight read; below that
+//    the smaller tiles' last round is fuller;
 //  * O / down (N = d): 128-column tiles with split-K; up to 128 rows O takes
 //    64-column tiles and split-K 4, which halves the float32 partials of the
 //    8-way split.

@@ -246,7 +246,7 @@ hipError_t gemm_store_f32(const ActIn& a, int M, int K, const void* w, int N, fl
 size_t gemm_split_ws_floats(int M, int max_n);
 
 // bfloat16 LM head with the row statistics fused into the GEMM epilogue
-// (per half tile) and merged by a second kernel; logits stored only if
+// (per 64 columns) and merged by a second kernel; logits stored only if
 // `logits` is not null.  N must be a multiple of 128.
 size_t lm_stats_ws_bytes(int M, int N);
 hipError_t lm_head_stats(const ActIn& a, int M, int K, const void* w, int N, int mask_id, int k,

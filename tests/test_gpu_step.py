@@ -221,8 +221,8 @@ def test_llada_long_shape_2_layers_bf16(gpu):
 
 def test_llada_long_shape_2_layers_single_bf16_activations(gpu):
     """SSM_ACT_BF16 (projection inputs rounded once to bfloat16, one MFMA pass):
-    the 1264-row block-start step runs the big-tile GEMM without the lo part,
-    the 240-row cached step the 128-row kernel without it.  Two layers keep the
+    the 1264-row block-start step runs gemm_pp_kernel without the lo part, the
+    240-row cached step gemm_bf16_kernel without it.  Two layers keep the
     single rounding well inside the bound."""
     from paper_2608_23167_amd import _lib as L
     wl = sharpened(WORKLOADS["llada_long2048"], 30.0)
@@ -233,10 +233,10 @@ def test_llada_long_shape_2_layers_single_bf16_activations(gpu):
 @pytest.mark.parametrize("batch", [1, 2])
 def test_llada_shape_one_pass_512_and_1024_rows(gpu, batch):
     """One-pass (SSM_ACT_BF16) block-start step of block 5 of the gen-256
-    workload: 512 rows per sequence.  At batch 1 gate/up runs the 3-stage
-    256 x 128 tiles and QKV, O, down the 128-row kernel; at batch 2 (1024
-    rows) QKV the 256 x 128 tiles, gate/up the 256 x 256 tiles, O and down
-    the 256 x 256 tiles with split-K."""
+    workload: 512 rows per sequence.  All projections run on
+    gemm_pp_kernel: at batch 1 QKV on 128 x 192 tiles, gate/up on 256 x 192, O
+    and down on 256 x 128 with 4 splits; at batch 2 (1024 rows) QKV and gate/up
+    on 256 x 192, O and down on 256 x 128 with 2 splits."""
     from paper_2608_23167_amd import _lib as L
     wl = sharpened(WORKLOADS["llada_gen256"], 30.0)
     wl = wl.replace(model=wl.model.with_layers(2), batch=batch)
@@ -246,7 +246,7 @@ def test_llada_shape_one_pass_512_and_1024_rows(gpu, batch):
 def test_llada_long_shape_pair_in_first_layer_only(gpu):
     """SSM_ACT_BF16X2_FIRST with one pair layer: layer 0 multiplies the hi and
     lo parts, layer 1 and the LM head round once, on both the block-start
-    (1264 rows, big tiles) and the cached (240 rows) launch paths."""
+    (1264 rows, 256-row tiles) and the cached (240 rows) launch paths."""
     from paper_2608_23167_amd import _lib as L
     wl = sharpened(WORKLOADS["llada_long2048"], 30.0)
     wl = wl.replace(model=wl.model.with_layers(2))
@@ -255,8 +255,8 @@ def test_llada_long_shape_pair_in_first_layer_only(gpu):
 
 def test_llada_long1024_block_start_1776_rows_2_layers_bf16(gpu):
     """Block-start step of block 8 of the gen-1024 long workload: 1776 rows, a
-    ragged last tile for both the 256-row (gate/up: 256 x 256, 3-stage ring)
-    and the 128-row (O/down: 128 x 256, 3-stage ring) big-tile GEMMs."""
+    ragged last row tile in every projection (QKV on 256 x 192 tiles, gate/up on
+    256 x 256, O on 256 x 128)."""
     wl = sharpened(WORKLOADS["llada_long1024"], 30.0)
     wl = wl.replace(model=wl.model.with_layers(2))
     _bf16_case(wl, [(8, 1)])
