@@ -39,13 +39,13 @@ METRIC = "denoised tokens/sec + step latency per GPU (LLaDA-8B shape); % MFMA/HB
 TRAFFIC = {
     # rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE over `bench.py --steps 32 --warmup 1
     # --no-profile --no-cpu-baseline --no-full-suffix --no-mfma --no-gen-sweep`:
-    # per-dispatch means of the block-start launches (grid 393216, 376 rows) and
-    # the cached ones (grid 131072, 120 rows), for the one-pass layers and the
-    # layers that keep the bfloat16 pair; copy kernel: 268435456 bytes read and
+    # per-dispatch means of the block-start launches (376 rows) and the cached
+    # ones (120 rows), for the one-pass layers and the layers that keep the
+    # bfloat16 pair; copy kernel: 268435456 bytes read and
     # written per launch read as 131086.1 KiB fetched and 262144.0 KiB written
     ("llada_gen256", "gemm_gate_up"): {
-        "sources_sha256": "e9babf06dc649fb394273589dd248cba4496b0fc516fce905c7a3482e53c1c55",
-        "fetch_kib": {"start": (135810.6, 189390.7), "cached": (104448.8, 110535.8)},
+        "sources_sha256": "47cd58ba0e6ebf84be64ac5d5d45bc6f04955329946be96a2e1a5783eb6e308a",
+        "fetch_kib": {"start": (110713.2, 189483.4), "cached": (104469.6, 110570.3)},
         "write_kib": {"start": (9024.0, 18048.0), "cached": (2880.0, 5760.0)},
         "fetch_scale": 262144.0 / 131086.1, "write_scale": 1.0},
 }
