@@ -44,8 +44,8 @@ TRAFFIC = {
     # bfloat16 pair; copy kernel: 268435456 bytes read and
     # written per launch read as 131086.1 KiB fetched and 262144.0 KiB written
     ("llada_gen256", "gemm_gate_up"): {
-        "sources_sha256": "47cd58ba0e6ebf84be64ac5d5d45bc6f04955329946be96a2e1a5783eb6e308a",
-        "fetch_kib": {"start": (110713.2, 189483.4), "cached": (104469.6, 110570.3)},
+        "sources_sha256": "d92d41d2440baf5003b65515d772004377ba01781f83132f60162a5cdf2d5554",
+        "fetch_kib": {"start": (110712.9, 189577.9), "cached": (104469.6, 110566.0)},
         "write_kib": {"start": (9024.0, 18048.0), "cached": (2880.0, 5760.0)},
         "fetch_scale": 262144.0 / 131086.1, "write_scale": 1.0},
 }

@@ -439,8 +439,8 @@ __device__ __forceinline__ void lds_written_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
-// Warp-specialised workgroup of 8 waves, BM rows (64, 128, 192 or 256) x BN
-// columns.
+// Warp-specialised workgroup of 8 waves, BM rows (128 or 256; 64 and 192 in a
+// tuning build) x BN columns.
 //  * Waves 4-7 ("staging") stream the weight tile of each K-step (BN rows x 64
 //    k, the HBM-bound stream) through a ring of 4 register stages into a ring
 //    of 3 or 4 LDS buffers, 2 or 3 K-steps ahead.  A staging thread holds only BN / 32
@@ -1055,6 +1055,9 @@ size_t gemm_split_ws_floats(int M, int max_n) {
 // Tiles of gemm_pp_kernel: rows, columns and the time of a K-step of 64 in a
 // full round of 256 workgroups (one per CU), in us.  A round of workgroups
 // takes steps * us + PP_FIXED_US (prologue, first copies, epilogue, launch).
+// That holds for several rounds (gate/up of 1776 rows: 297 us, 291 in a trace);
+// a launch of one round takes 18-23 us more in a stack of layers (476 rows:
+// gate/up 77 and 99 us, QKV 50 and 70).
 // Measured in a loop of 1024-2048 x 4096-8192 x 4096 products with random
 // operands: the 256 x 256 tile takes 2415 clocks for the 2048 clocks of MFMAs
 // that a K-step holds per SIMD, the smaller ones 1990 for 1536, 1600 and 1660
@@ -1086,8 +1089,8 @@ static float bf16_step_us(int bn, int bm, bool pair) {
 }
 
 // Per-projection launch choice: tile width BN (64, 96 or 128), split-K S
-// (0 = automatic) and the depth PW (4 or 8 K-steps) of the staging waves'
-// register ring of weight loads of gemm_bf16_kernel, with its row tile bm
+// (0 = automatic) and the depth PW (4 K-steps, in a tuning build also 8) of the
+// staging waves' register ring of weight loads of gemm_bf16_kernel, with its row tile bm
 // (see launch_bf16_bm); or, with pp = 1 + an index into PP_TILES,
 // gemm_pp_kernel (-1: the tile and split that cost least).
 struct GemmCfg {
